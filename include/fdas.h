@@ -115,11 +115,12 @@ int fdas_prepare_bank(const fdas_cf32 *taps_dev, int K, int M, int L,
                       fdas_cf32 *bank_dev, hipStream_t stream);
 
 /*
- * Templates for the grid (zmax, dz) with M taps, computed on the host in
- * FP64 and copied to taps_dev (K*M elements, required); if bank_dev is not
- * NULL the bank for segment length L is prepared from those taps as by
- * fdas_prepare_bank (L is ignored when bank_dev is NULL).  Blocks the host
- * until the copy has been consumed.  Not on the hot path.
+ * Templates for the grid (zmax, dz) with M taps, computed on the device in
+ * FP64 and rounded once into taps_dev (K*M elements, required), equal bit
+ * for bit to fdas_make_templates_host; if bank_dev is not NULL the bank for
+ * segment length L is prepared from those taps as by fdas_prepare_bank (L is
+ * ignored when bank_dev is NULL).  Synchronises the stream.  Not on the hot
+ * path.
  */
 int fdas_make_templates(double zmax, double dz, int M, int L,
                         fdas_cf32 *taps_dev, fdas_cf32 *bank_dev,

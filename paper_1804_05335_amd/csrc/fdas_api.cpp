@@ -6,8 +6,6 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
-#include <new>
-#include <vector>
 
 #include "../../include/fdas.h"
 #include "fdas_internal.h"
@@ -87,25 +85,6 @@ void fill_templates(double dz, int K, int M, fdas_cf32* out)
             const std::complex<double> r = fdas::response(double(j - M / 2), z);
             out[(size_t)k * M + j].re = (float)r.real();
             out[(size_t)k * M + j].im = (float)r.imag();
-        }
-    }
-}
-
-// Half-bin taps of the two-bin Fourier interpolation, K x (M + 2): tap j of
-// template z sits at bin offset j - (M+2)/2 and holds R(1/2 - offset, z) for
-// the M offsets -M/2+1 .. M/2 (the bins centred on the half bin); taps 0 and
-// 1 are zero.
-void fill_templates_half(double dz, int K, int M, fdas_cf32* out)
-{
-    const int Mh = M + 2;
-    for (int k = 0; k < K; ++k) {
-        const double z = (double(k) - 0.5 * double(K - 1)) * dz;
-        for (int j = 0; j < Mh; ++j) {
-            std::complex<double> r(0.0, 0.0);
-            if (j >= 2)
-                r = fdas::response(0.5 - double(j - Mh / 2), z);
-            out[(size_t)k * Mh + j].re = (float)r.real();
-            out[(size_t)k * Mh + j].im = (float)r.imag();
         }
     }
 }
@@ -217,24 +196,17 @@ int fdas_make_templates(double zmax, double dz, int M, int L, fdas_cf32* taps_de
     } else if (M < 2 || (M & 1) || M > 16384) {
         return fail(FDAS_UNSUPPORTED, "M = %d must be even in [2, 16384]", M);
     }
-    std::vector<fdas_cf32> host;
-    try {
-        host.resize((size_t)K * M);
-    } catch (const std::bad_alloc&) {
-        return fail(FDAS_INVALID_ARG, "host allocation of %d x %d taps failed", K, M);
-    }
-    fill_templates(dz, K, M, host.data());
-    hipError_t e = hipMemcpyAsync(taps_dev, host.data(), host.size() * sizeof(fdas_cf32),
-                                  hipMemcpyHostToDevice, stream);
+    hipError_t e = fdas::launch_templates(dz, K, M, false, reinterpret_cast<float2*>(taps_dev),
+                                          stream);
     if (e != hipSuccess)
-        return hip_fail(e, "copy of taps to the device");
+        return hip_fail(e, "templates launch");
     if (bank_dev) {
         e = fdas::launch_prepare_bank(reinterpret_cast<const float2*>(taps_dev), K, M, L,
                                       reinterpret_cast<float2*>(bank_dev), stream);
         if (e != hipSuccess)
             return hip_fail(e, "prepare_bank launch");
     }
-    e = hipStreamSynchronize(stream);   // the host copy must outlive the transfer
+    e = hipStreamSynchronize(stream);   // finished on return, for callers on any stream
     if (e != hipSuccess)
         return hip_fail(e, "stream synchronize");
     return ok();
@@ -358,24 +330,17 @@ int fdas_make_templates_half(double zmax, double dz, int M, int L, fdas_cf32* ta
         return fail(FDAS_INVALID_ARG, "taps_half_dev is NULL");
     if (!aligned(taps_half_dev, 8) || (bank_half_dev && !aligned(bank_half_dev, 16)))
         return fail(FDAS_INVALID_ARG, "taps_half_dev must be 8-byte and bank_half_dev 16-byte aligned");
-    std::vector<fdas_cf32> host;
-    try {
-        host.resize((size_t)K * (M + 2));
-    } catch (const std::bad_alloc&) {
-        return fail(FDAS_INVALID_ARG, "host allocation of %d x %d taps failed", K, M + 2);
-    }
-    fill_templates_half(dz, K, M, host.data());
-    hipError_t e = hipMemcpyAsync(taps_half_dev, host.data(), host.size() * sizeof(fdas_cf32),
-                                  hipMemcpyHostToDevice, stream);
+    hipError_t e = fdas::launch_templates(dz, K, M + 2, true,
+                                          reinterpret_cast<float2*>(taps_half_dev), stream);
     if (e != hipSuccess)
-        return hip_fail(e, "copy of half-bin taps to the device");
+        return hip_fail(e, "half-bin templates launch");
     if (bank_half_dev) {
         e = fdas::launch_prepare_bank(reinterpret_cast<const float2*>(taps_half_dev), K, M + 2, L,
                                       reinterpret_cast<float2*>(bank_half_dev), stream);
         if (e != hipSuccess)
             return hip_fail(e, "prepare_bank launch");
     }
-    e = hipStreamSynchronize(stream);   // the host copy must outlive the transfer
+    e = hipStreamSynchronize(stream);   // finished on return, for callers on any stream
     if (e != hipSuccess)
         return hip_fail(e, "stream synchronize");
     return ok();

@@ -12,8 +12,12 @@ namespace fdas {
 // Record `msg` as the calling thread's last-error text and return status.
 int fail_status(int status, const char* msg);
 
-// Host FP64 response R(q, z) (templates source file).
+// Host FP64 response R(q, z) (fdas_response.hpp).
 std::complex<double> response(double q, double z);
+
+// Templates of the grid (Mt taps per row; half: the half-bin taps) into
+// taps [K][Mt], equal bit for bit to response() rounded to FP32.
+hipError_t launch_templates(double dz, int K, int Mt, bool half, float2* taps, hipStream_t s);
 
 // Bank rows H_z and the twiddle row for segment length L.
 hipError_t launch_prepare_bank(const float2* taps, int K, int M, int L, float2* bank,

@@ -9,6 +9,7 @@
 
 #include "fdas_fft.hpp"
 #include "fdas_internal.h"
+#include "fdas_response.hpp"
 
 namespace fdas {
 
@@ -43,58 +44,182 @@ __device__ __forceinline__ int seg_off(int q, int half_m)
     return q >= half_m ? q * BYTES : (int)0x80000000u;
 }
 
-// ---- bank preparation (off the hot path) ------------------------------------
+// ---- templates and bank preparation -------------------------------------------
 //
-// H_z[k] = (1/L) sum_j conj(T[z][j]) W_L^{((M/2 - j) mod L) k}: tap j of the
-// template placed so that the filter is centred on bin 0, its two halves at
-// the ends of the L-array (Sec. 3, Fig. 1).  Accumulated in FP64 with exact
-// integer phase indices; one lane per (z, k).
-__global__ void bank_rows_kernel(const float2* __restrict__ taps, int K, int M, int L,
-                                 float2* __restrict__ bank)
+// Templates of the grid (Sec. 2, text before eq. 23), one lane per tap:
+// taps[k][j] = R(j - M/2, z_k), z_k = (k - (K-1)/2) dz, or with HALF the
+// half-bin taps of the two-bin interpolation, taps[k][j] = R(1/2 - (j -
+// Mt/2), z_k) for j >= 2 and 0 below.  Mt is the row length.  Bound by one
+// lane's FP64 chain (up to ~40 steps of a continued fraction or a series per
+// end of the integral), so the lanes are spread over as many one-wave
+// workgroups as there are: 10 us at K = 85, M = 256, where the host took 8 ms
+// of one core and a blocking copy.
+constexpr int kTemplateThreads = 64;
+
+template <bool HALF>
+__global__ __launch_bounds__(kTemplateThreads) void templates_kernel(double dz, int K, int Mt,
+                                                                     float2* __restrict__ taps)
 {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    const int z = blockIdx.y;
-    if (k >= L || z >= K)
+    const int i = blockIdx.x * kTemplateThreads + threadIdx.x;
+    if (i >= K * Mt)
         return;
-    const float2* tz = taps + (int64_t)z * M;
-    double sr = 0.0, si = 0.0;
-    for (int j = 0; j < M; ++j) {
-        int n = (M / 2 - j) % L;
-        if (n < 0)
-            n += L;
-        const int64_t p = ((int64_t)n * k) & (L - 1);
-        double s, c;
-        sincospi(-2.0 * (double)p / (double)L, &s, &c);
-        const float2 t = tz[j];
-        const double hr = t.x, hi = -t.y;   // conj(T)
-        sr += hr * c - hi * s;
-        si += hr * s + hi * c;
-    }
-    const double inv = 1.0 / (double)L;
-    bank[(int64_t)z * L + k] = make_float2((float)(sr * inv), (float)(si * inv));
+    const int k = i / Mt, j = i - k * Mt;
+    const double z = ((double)k - 0.5 * (double)(K - 1)) * dz;
+    cplx64 r = {0.0, 0.0};
+    if (!HALF || j >= 2)
+        r = response64(HALF ? 0.5 - (double)(j - Mt / 2) : (double)(j - Mt / 2), z);
+    taps[i] = make_float2((float)r.re, (float)r.im);
 }
 
-// Twiddle row: exp(-2 pi i n / L), n in [0, L), FP64 rounded once.
-__global__ void bank_twiddle_kernel(int K, int L, float2* __restrict__ bank)
+hipError_t launch_templates(double dz, int K, int Mt, bool half, float2* taps, hipStream_t s)
 {
-    const int n = blockIdx.x * blockDim.x + threadIdx.x;
-    if (n >= L)
-        return;
+    const dim3 grid((unsigned)(((int64_t)K * Mt + kTemplateThreads - 1) / kTemplateThreads));
+    if (half)
+        hipLaunchKernelGGL((templates_kernel<true>), grid, dim3(kTemplateThreads), 0, s, dz, K, Mt,
+                           taps);
+    else
+        hipLaunchKernelGGL((templates_kernel<false>), grid, dim3(kTemplateThreads), 0, s, dz, K,
+                           Mt, taps);
+    return hipGetLastError();
+}
+
+// H_z[k] = (1/L) sum_j conj(T[z][j]) W_L^{((M/2 - j) mod L) k}: tap j of the
+// template placed so that the filter is centred on bin 0, its two halves at
+// the ends of the L-array (Sec. 3, Fig. 1); accumulated in FP64.
+//
+// With v = W_L^{-k} the sum is W_L^{(M/2) k} sum_j c_j v^j, c = conj T.  A
+// lane takes the eight rows k = k0 + m L/8: v^8 is the same for all of them,
+// so it evaluates S_b = sum_a c_{8a+b} (v^8)^a, b < 8, once, by Horner's rule
+// (eight independent chains of four FP64 FMAs per tap), and combines them
+// with one eight-point transform of S_b W_L^{-b k0}.  Few lanes and short
+// chains: the row's taps come from LDS (scalar loads in the loop waited for
+// memory once per group of taps: 17 us), and one sine and cosine pair serves
+// all the powers W_L^{-b k0} (a pair for each took 16 of them per lane).
+// Measured: 8-10 us at K = 85, M = 256, L = 2048 and 43 us at K = 201, M =
+// 512, L = 8192; one lane per (z, k) with a sine and cosine per tap took 151
+// and 2031 us with its launch for the twiddles.
+// The row z = K holds the twiddles exp(-2 pi i n / L).
+constexpr int kBankThreads = 64;
+
+// Row lengths the LDS copy is sized for: the ordinary banks, whose small copy
+// leaves room for many workgroups per CU, and the longest (L/2 at L = 8192).
+constexpr int kBankTaps = 512, kBankMaxTaps = 4096;
+
+__device__ __forceinline__ cplx64 bank_root(int64_t p, int L)   // W_L^p
+{
     double s, c;
-    sincospi(-2.0 * (double)n / (double)L, &s, &c);
-    bank[(int64_t)K * L + n] = make_float2((float)c, (float)s);
+    sincospi(-2.0 * (double)(p & (L - 1)) / (double)L, &s, &c);
+    return {c, s};
+}
+
+__device__ __forceinline__ void bank_bfly(cplx64& a, cplx64& b)
+{
+    const cplx64 d = a - b;
+    a = a + b;
+    b = d;
+}
+
+template <int MAXM>
+__global__ __launch_bounds__(kBankThreads) void bank_rows_kernel(const float2* __restrict__ taps,
+                                                                 int K, int M, int L,
+                                                                 float2* __restrict__ bank)
+{
+    __shared__ float2 tz[MAXM];
+    const int k0 = blockIdx.x * kBankThreads + threadIdx.x;
+    const int z = blockIdx.y;
+    const int P = L / 8;
+    float2* row = bank + (int64_t)z * L + k0;
+    if (z == K) {
+#pragma unroll
+        for (int m = 0; m < 8; ++m)
+            if (k0 < P) {
+                const cplx64 w = bank_root(k0 + m * P, L);
+                row[m * P] = make_float2((float)w.re, (float)w.im);
+            }
+        return;
+    }
+    for (int j = threadIdx.x; j < M; j += kBankThreads)
+        tz[j] = taps[(int64_t)z * M + j];
+    const cplx64 v8 = bank_root(-8 * (int64_t)k0, L);
+    const cplx64 v1 = bank_root(-(int64_t)k0, L);
+    const cplx64 centre = bank_root((int64_t)(M / 2) * k0, L);
+    __syncthreads();
+    cplx64 S[8];
+#pragma unroll
+    for (int b = 0; b < 8; ++b)
+        S[b] = {0.0, 0.0};
+    auto step = [&](int b, float2 t) {           // S <- S v^8 + conj(t)
+        const double re = fma(S[b].re, v8.re, (double)t.x);
+        const double im = fma(S[b].re, v8.im, -(double)t.y);
+        S[b] = {fma(-S[b].im, v8.im, re), fma(S[b].im, v8.re, im)};
+    };
+    int a = M / 8 * 8;
+    if (a < M) {                                 // the last, shorter group of taps
+#pragma unroll
+        for (int b = 0; b < 8; ++b)
+            if (a + b < M)
+                step(b, tz[a + b]);
+    }
+#pragma unroll 2
+    for (a -= 8; a >= 0; a -= 8) {
+#pragma unroll
+        for (int b = 0; b < 8; ++b)
+            step(b, tz[a + b]);
+    }
+    // S_b <- S_b v^b
+    const cplx64 v2 = v1 * v1, v4 = v2 * v2, v3 = v2 * v1;
+    S[1] = S[1] * v1;
+    S[2] = S[2] * v2;
+    S[3] = S[3] * v3;
+    S[4] = S[4] * v4;
+    S[5] = S[5] * (v4 * v1);
+    S[6] = S[6] * (v4 * v2);
+    S[7] = S[7] * (v4 * v3);
+    // X[m] = sum_b S[b] e^{+2 pi i b m / 8}
+    const double h = 0.70710678118654752440084436210485;
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+        bank_bfly(S[b], S[b + 4]);
+    S[5] = cplx64{S[5].re - S[5].im, S[5].re + S[5].im} * h;
+    S[6] = {-S[6].im, S[6].re};
+    S[7] = cplx64{-(S[7].re + S[7].im), S[7].re - S[7].im} * h;
+#pragma unroll
+    for (int g = 0; g < 8; g += 4) {
+        bank_bfly(S[g], S[g + 2]);
+        bank_bfly(S[g + 1], S[g + 3]);
+        S[g + 3] = {-S[g + 3].im, S[g + 3].re};
+        bank_bfly(S[g], S[g + 1]);
+        bank_bfly(S[g + 2], S[g + 3]);
+    }
+    if (k0 >= P)
+        return;
+    // times W_L^{(M/2)(k0 + m L/8)} / L = W_L^{(M/2) k0} W_8^{(M/2) m} / L
+    const double inv = 1.0 / (double)L;
+#pragma unroll
+    for (int m = 0; m < 8; ++m) {
+        // the decimation leaves X[m] at the bit-reversed place
+        cplx64 r = S[((m & 1) << 2) | (m & 2) | (m >> 2)] * centre;
+        const int e = (M / 2 * m) & 7;           // uniform: eighth turns
+        if (e & 1)
+            r = cplx64{r.re + r.im, r.im - r.re} * h;
+        if (e & 2)
+            r = {r.im, -r.re};
+        if (e & 4)
+            r = {-r.re, -r.im};
+        row[m * P] = make_float2((float)(r.re * inv), (float)(r.im * inv));
+    }
 }
 
 hipError_t launch_prepare_bank(const float2* taps, int K, int M, int L, float2* bank,
                                hipStream_t s)
 {
-    const int bs = 256;
-    dim3 grid((L + bs - 1) / bs, K);
-    hipLaunchKernelGGL(bank_rows_kernel, grid, dim3(bs), 0, s, taps, K, M, L, bank);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess)
-        return e;
-    hipLaunchKernelGGL(bank_twiddle_kernel, dim3((L + bs - 1) / bs), dim3(bs), 0, s, K, L, bank);
+    const dim3 grid((L / 8 + kBankThreads - 1) / kBankThreads, K + 1);
+    if (M <= kBankTaps)
+        hipLaunchKernelGGL((bank_rows_kernel<kBankTaps>), grid, dim3(kBankThreads), 0, s, taps, K,
+                           M, L, bank);
+    else
+        hipLaunchKernelGGL((bank_rows_kernel<kBankMaxTaps>), grid, dim3(kBankThreads), 0, s, taps,
+                           K, M, L, bank);
     return hipGetLastError();
 }
 

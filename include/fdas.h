@@ -520,6 +520,17 @@ int fdas_harmonic_shape(int64_t N, int K, int H, int *KH, int64_t *NH);
 int fdas_harmonic_sum(const float *plane_dev, int64_t N, int K, int H, const float *prev_dev,
                       float *sums_dev, hipStream_t stream);
 
+/*
+ * Folds 2, 4, .., max_fold of one plane in one launch, each built on the one
+ * below without reading it back: sums_dev (a host array of log2(max_fold)
+ * device pointers, read before the call returns) gets S_2, S_4, .. in the
+ * layout of fdas_harmonic_sum, bitwise the same.  max_fold: a power of two in
+ * [1, 64] (1 is a no-op).  The folds overlap neither the plane nor one
+ * another.  Asynchronous on `stream`; no allocation.
+ */
+int fdas_harmonic_sums(const float *plane_dev, int64_t N, int K, int max_fold,
+                       float *const *sums_dev, hipStream_t stream);
+
 /* One candidate: the fundamental's frequency bin, its template row in the
  * plane (z = (row - (K-1)/2) dz) and its H-fold summed power. */
 typedef struct {
@@ -559,6 +570,19 @@ size_t fdas_harmonic_batched_workspace_bytes(int nspec);
 int fdas_harmonic_sum_batched(const float *planes_dev, const int64_t *offsets_dev, int nspec,
                               int K, int H, const float *prev_dev, float *sums_dev, void *ws_dev,
                               size_t ws_bytes, hipStream_t stream);
+
+/*
+ * Folds 2 .. max_fold of every spectrum in one launch after a scan, as
+ * fdas_harmonic_sums for one plane: sums_dev is a host array of log2(max_fold)
+ * device pointers, fold H laid out as by fdas_harmonic_sum_batched and bitwise
+ * the same.  capacity: the bins planes_dev holds (its floats over K), which
+ * sizes the launch.  ws_dev: fdas_harmonic_sums_batched_workspace_bytes(nspec) bytes
+ * (8-byte aligned, scratch).  Capturable in a graph.
+ */
+size_t fdas_harmonic_sums_batched_workspace_bytes(int nspec);
+int fdas_harmonic_sums_batched(const float *planes_dev, const int64_t *offsets_dev, int nspec,
+                               int64_t capacity, int K, int max_fold, float *const *sums_dev,
+                               void *ws_dev, size_t ws_bytes, hipStream_t stream);
 
 /*
  * Candidates of fold H of every spectrum (sums_dev as written by

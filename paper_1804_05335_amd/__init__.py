@@ -22,6 +22,8 @@ from ._lib import (FdasError, fdas_backward_workspace_bytes, fdas_bank_elems,  #
                    fdas_correlate_fourier2_ex, fdas_harmonic_shape, fdas_harmonic_sum,
                    fdas_find_candidates, fdas_harmonic_batched_workspace_bytes,
                    fdas_harmonic_sum_batched, fdas_find_candidates_batched,
+                   fdas_harmonic_sums, fdas_harmonic_sums_batched,
+                   fdas_harmonic_sums_batched_workspace_bytes,
                    fdas_stream_write, fdas_stream_read, fdas_r2c_batched,
                    fdas_r2c_batched_workspace_bytes, fdas_correlate_backward_batched,
                    fdas_backward_batched_workspace_bytes, fdas_autotune_batched,
@@ -198,17 +200,17 @@ def correlate_fourier2(spec, bank, bank_half, K: int, M: int, L: int, plane2=Non
 
 def harmonic_sums(plane, max_fold: int):
     """[S_1 = plane, S_2, S_4, ..., S_max_fold] of a [K][N] float32 plane
-    (Sec. 3 harmonic summing), each fold built on the previous one."""
+    (Sec. 3 harmonic summing), all folds in one launch."""
     import torch
     K, N = plane.shape
     folds = [plane]
     H = 2
     while H <= max_fold:
-        KH, NH = fdas_harmonic_shape(N, K, H)
-        out = torch.empty((KH, NH), dtype=torch.float32, device=plane.device)
-        fdas_harmonic_sum(plane, N, K, H, folds[-1] if H > 2 else None, out)
-        folds.append(out)
+        folds.append(torch.empty(fdas_harmonic_shape(N, K, H), dtype=torch.float32,
+                                 device=plane.device))
         H *= 2
+    if len(folds) > 1:
+        fdas_harmonic_sums(plane, N, K, H // 2, folds[1:])
     return folds
 
 
@@ -268,25 +270,23 @@ def fold_prefix(offsets_host, H: int):
 def harmonic_sums_batched(planes, offsets, K: int, max_fold: int):
     """Folds 2, 4, .., max_fold of the planes of correlate_batched (flat
     float32 device tensor; offsets the int64 device tensor of nspec + 1
-    packed-bin offsets), each fold built on the previous one in one launch
-    for all spectra.  Returns the list [planes, S_2, S_4, ...] of flat
+    packed-bin offsets), all folds of all spectra in one launch.  Returns the list [planes, S_2, S_4, ...] of flat
     tensors; fold H of spectrum b is S_H[K_H C_H[b] : K_H C_H[b+1]] viewed
     as [K_H][ceil(N_b/H)] (see fold_prefix)."""
     import torch
     offs = offsets.cpu().numpy()
     nspec = len(offs) - 1
-    ws = torch.empty(max(fdas_harmonic_batched_workspace_bytes(nspec), 1), dtype=torch.uint8,
-                     device=planes.device)
+    ws = torch.empty(max(fdas_harmonic_sums_batched_workspace_bytes(nspec), 1),
+                     dtype=torch.uint8, device=planes.device)
     folds = [planes]
     H = 2
     while H <= max_fold:
         KH, _ = fdas_harmonic_shape(0, K, H)
         total = int(fold_prefix(offs, H)[-1])
-        out = torch.empty(max(KH * total, 1), dtype=torch.float32, device=planes.device)
-        fdas_harmonic_sum_batched(planes, offsets, nspec, K, H, folds[-1] if H > 2 else None,
-                                  out, ws)
-        folds.append(out)
+        folds.append(torch.empty(max(KH * total, 1), dtype=torch.float32, device=planes.device))
         H *= 2
+    if len(folds) > 1:
+        fdas_harmonic_sums_batched(planes, offsets, nspec, K, H // 2, folds[1:], ws)
     return folds
 
 

@@ -66,9 +66,12 @@ SIGNATURES = [
     ("fdas_r2c", _I, [_P, _I64, ctypes.c_float, _P, _P, _SZ, _P]),
     ("fdas_harmonic_shape", _I, [_I64, _I, _I, ctypes.POINTER(_I), ctypes.POINTER(_I64)]),
     ("fdas_harmonic_sum", _I, [_P, _I64, _I, _I, _P, _P, _P]),
+    ("fdas_harmonic_sums", _I, [_P, _I64, _I, _I, _P, _P]),
     ("fdas_find_candidates", _I, [_P, _I64, _I, _I, ctypes.c_float, _P, _I, _P, _P]),
     ("fdas_harmonic_batched_workspace_bytes", _SZ, [_I]),
     ("fdas_harmonic_sum_batched", _I, [_P, _P, _I, _I, _I, _P, _P, _P, _SZ, _P]),
+    ("fdas_harmonic_sums_batched_workspace_bytes", _SZ, [_I]),
+    ("fdas_harmonic_sums_batched", _I, [_P, _P, _I, _I64, _I, _I, _P, _P, _SZ, _P]),
     ("fdas_find_candidates_batched", _I, [_P, _P, _I, _I, _I, ctypes.c_float, _P, _I, _P, _P,
                                           _SZ, _P]),
     ("fdas_r2c_batched_workspace_bytes", _SZ, [_I64, _I]),
@@ -496,6 +499,26 @@ def fdas_harmonic_sum(plane, N: int, K: int, H: int, prev, sums, stream=None) ->
                                    _stream(stream, plane)), "fdas_harmonic_sum")
 
 
+def _pointers(tensors):
+    """A host array of the tensors' device pointers."""
+    return (ctypes.c_void_p * max(len(tensors), 1))(*[t.data_ptr() for t in tensors])
+
+
+def fdas_harmonic_sums(plane, N: int, K: int, max_fold: int, sums, stream=None) -> None:
+    """sums: the float32 device tensors of folds 2, 4, .., max_fold."""
+    import torch
+    _require(plane, torch.float32, "plane", K * N)
+    H = 2
+    for S in sums:
+        KH, NH = fdas_harmonic_shape(N, K, H)
+        _require(S, torch.float32, "sums", KH * NH)
+        H *= 2
+    if H != 2 * max_fold:
+        raise ValueError(f"{len(sums)} sums for folds 2..{max_fold}")
+    _check(lib().fdas_harmonic_sums(_ptr(plane), N, K, max_fold, _pointers(sums),
+                                    _stream(stream, plane)), "fdas_harmonic_sums")
+
+
 def fdas_find_candidates(sums, N: int, K: int, H: int, threshold: float, out, capacity: int,
                          count, stream=None) -> None:
     """out: uint8 device tensor of capacity * 16 bytes (fdas_candidate
@@ -530,6 +553,28 @@ def fdas_harmonic_sum_batched(planes, offsets, nspec: int, K: int, H: int, prev,
                                            _ptr(sums), _ptr(ws), ws.numel(),
                                            _stream(stream, planes)),
            "fdas_harmonic_sum_batched")
+
+
+def fdas_harmonic_sums_batched_workspace_bytes(nspec: int) -> int:
+    return int(lib().fdas_harmonic_sums_batched_workspace_bytes(nspec))
+
+
+def fdas_harmonic_sums_batched(planes, offsets, nspec: int, K: int, max_fold: int, sums, ws,
+                               stream=None) -> None:
+    """sums: the float32 device tensors of folds 2, 4, .., max_fold (their
+    sizes are the caller's, as in fdas_harmonic_sum_batched)."""
+    import torch
+    _require(planes, torch.float32, "planes")
+    _require(offsets, torch.int64, "offsets", nspec + 1)
+    for S in sums:
+        _require(S, torch.float32, "sums")
+    if 1 << len(sums) != max_fold:
+        raise ValueError(f"{len(sums)} sums for folds 2..{max_fold}")
+    _require(ws, torch.uint8, "ws", fdas_harmonic_sums_batched_workspace_bytes(nspec))
+    _check(lib().fdas_harmonic_sums_batched(_ptr(planes), _ptr(offsets), nspec,
+                                            planes.numel() // K, K, max_fold, _pointers(sums),
+                                            _ptr(ws), ws.numel(), _stream(stream, planes)),
+           "fdas_harmonic_sums_batched")
 
 
 def fdas_find_candidates_batched(sums, offsets, nspec: int, K: int, H: int, threshold: float,

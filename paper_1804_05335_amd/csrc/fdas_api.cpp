@@ -829,6 +829,38 @@ int fdas_harmonic_sum(const float* plane_dev, int64_t N, int K, int H, const flo
     return ok();
 }
 
+int fdas_harmonic_sums(const float* plane_dev, int64_t N, int K, int max_fold,
+                       float* const* sums_dev, hipStream_t stream)
+{
+    const int st = check_harmonic(N, K, max_fold);
+    if (st)
+        return st;
+    if (max_fold == 1 || N == 0)
+        return ok();
+    if (!plane_dev || !sums_dev || !aligned(plane_dev, 4))
+        return fail(FDAS_INVALID_ARG, "plane and sums must not be NULL, plane 4-byte aligned");
+    size_t bytes[8] = {};
+    int folds = 0;
+    for (int H = 2; H <= max_fold; H *= 2, ++folds) {
+        int KH = 0;
+        int64_t NH = 0;
+        fdas::harmonic_shape(N, K, H, &KH, &NH);
+        bytes[folds] = (size_t)KH * (size_t)NH * sizeof(float);
+        if (!sums_dev[folds] || !aligned(sums_dev[folds], 4))
+            return fail(FDAS_INVALID_ARG, "the %d-fold sums must be a 4-byte aligned pointer", H);
+        if (overlaps(sums_dev[folds], bytes[folds], plane_dev, (size_t)K * (size_t)N * sizeof(float)))
+            return fail(FDAS_INVALID_ARG, "sums must not overlap the plane");
+        for (int i = 0; i < folds; ++i)
+            if (overlaps(sums_dev[folds], bytes[folds], sums_dev[i], bytes[i]))
+                return fail(FDAS_INVALID_ARG, "the folds' sums must not overlap");
+    }
+    const hipError_t e =
+        fdas::launch_fold_chain(plane_dev, N, K, nullptr, 1, folds, sums_dev, stream);
+    if (e != hipSuccess)
+        return hip_fail(e, "harmonic sums launch");
+    return ok();
+}
+
 int fdas_find_candidates(const float* sums_dev, int64_t N, int K, int H, float threshold,
                          fdas_candidate* out_dev, int capacity, unsigned* count_dev,
                          hipStream_t stream)
@@ -908,6 +940,42 @@ int fdas_harmonic_sum_batched(const float* planes_dev, const int64_t* offsets_de
                                                        stream);
     if (e != hipSuccess)
         return hip_fail(e, "batched harmonic sum launch");
+    return ok();
+}
+
+size_t fdas_harmonic_sums_batched_workspace_bytes(int nspec)
+{
+    if (nspec < 0 || nspec > kMaxSpectra)
+        return 0;
+    const size_t b = 7 * ((size_t)nspec + 1) * sizeof(int64_t);
+    return (b + 255) & ~(size_t)255;
+}
+
+int fdas_harmonic_sums_batched(const float* planes_dev, const int64_t* offsets_dev, int nspec,
+                               int64_t capacity, int K, int max_fold, float* const* sums_dev,
+                               void* ws_dev, size_t ws_bytes, hipStream_t stream)
+{
+    const int st = check_harmonic_batched(offsets_dev, nspec, K, max_fold, ws_dev, ws_bytes);
+    if (st)
+        return st;
+    if (capacity < 0 || capacity > kMaxCapacity)
+        return fail(FDAS_INVALID_ARG, "capacity = %lld outside [0, 2^40]", (long long)capacity);
+    if (nspec == 0 || max_fold == 1)
+        return ok();
+    if (ws_bytes < fdas_harmonic_sums_batched_workspace_bytes(nspec))
+        return fail(FDAS_WORKSPACE_TOO_SMALL, "workspace has %zu bytes, needs %zu", ws_bytes,
+                    fdas_harmonic_sums_batched_workspace_bytes(nspec));
+    if (!planes_dev || !sums_dev || !aligned(planes_dev, 4))
+        return fail(FDAS_INVALID_ARG, "planes and sums must not be NULL, planes 4-byte aligned");
+    int folds = 0;
+    for (int H = 2; H <= max_fold; H *= 2, ++folds)
+        if (!sums_dev[folds] || !aligned(sums_dev[folds], 4))
+            return fail(FDAS_INVALID_ARG, "the %d-fold sums must be a 4-byte aligned pointer", H);
+    const hipError_t e =
+        fdas::launch_fold_chain_batched(planes_dev, offsets_dev, nspec, capacity, K, folds,
+                                        sums_dev, static_cast<int64_t*>(ws_dev), stream);
+    if (e != hipSuccess)
+        return hip_fail(e, "batched harmonic sums launch");
     return ok();
 }
 

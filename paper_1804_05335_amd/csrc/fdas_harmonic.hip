@@ -15,8 +15,8 @@
 // Memory: the plane is read with stride h along a row for harmonic h, so
 // each harmonic touches whole rows of the plane; folding up to 2^f reads
 // about half a plane per fold on top of the previous fold's sums.  The
-// kernels are plain streaming gathers (HBM-bound); a lane owns one
-// fundamental column and walks its harmonics with independent loads.
+// kernels are gathers bound by the lines they fetch; a lane owns a few
+// fundamental columns and walks their harmonics with independent loads.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -29,52 +29,182 @@ namespace fdas {
 namespace {
 
 constexpr int kHarmThreads = 256;
+constexpr int kHScanThreads = 256;
 
-// One row of the H-fold sum per blockIdx.y, kHarmCols columns per
-// blockIdx.x: lane t takes columns t + kHarmThreads j, j < kHarmCols /
-// kHarmThreads, so each load instruction is coalesced and every lane keeps
-// several independent gathers in flight.  With prev (the H/2-fold, KHp x
-// NHp), the sum starts from it and adds harmonics H/2 + 1 .. H; without, it
-// adds 1 .. H from zero.
-constexpr int kHarmPerLane = 4;
-constexpr int kHarmCols = kHarmThreads * kHarmPerLane;
+// ---- chains of folds on one plane ------------------------------------------------
+//
+// S_H[k][r] continues S_{H/2}[k][r] at the same (k, r), so one wave carries its
+// columns through all the folds whose domain holds them: the sums stay in
+// registers between folds, and each fold's new harmonics are loaded at once
+// (kFoldPerLane columns x kFoldGroup harmonics in flight per lane).
+//
+// Order of the work: harmonic 2h of the fundamental (k, r) is harmonic h of
+// (2k, 2r), so columns one octave apart share their plane lines.  The chunks
+// of kFoldCols columns are taken in an order in which chunk c and chunk 2c are
+// neighbours in time (fold_chunk), with all the rows of a chunk together, so
+// the shared lines are found in the caches: the plane lines of the even
+// harmonics then come from memory once per octave chain instead of once per
+// harmonic.
+//
+// Measured, folds 2..32 of a plane of 85 x 2^20: 119 us in one launch, 179 us
+// as one launch per fold that reads the fold below back; 165 us with the same
+// chains without the deal to the XCDs, and 122 / 136 us with runs of 16 / 8
+// places instead of 32 (64 and 128 the same as 32).
+constexpr int kFoldThreads = 64;      // one wave: its row is uniform
+constexpr int kFoldPerLane = 4;       // lane t takes columns t + 64 j
+constexpr int kFoldCols = kFoldThreads * kFoldPerLane;
+constexpr int kFoldGroup = 8;         // harmonics loaded before they are added
+constexpr int kMaxFolds = 7;          // H = 1, 2, .., 64
+constexpr int64_t kMaxFoldGridX = int64_t(1) << 22, kMaxFoldGridY = 1 << 15;
 
-__global__ __launch_bounds__(kHarmThreads) void harmonic_sum_kernel(
-    const float* __restrict__ plane, int64_t N, int K, int H, const float* __restrict__ prev,
-    int64_t NHp, int KHp, float* __restrict__ out, int64_t NH, int KH)
+struct FoldOut {
+    float* p[kMaxFolds];              // S_H at log2 H, or NULL
+};
+
+// The p-th chunk of the octave order on [0, P): an odd part q and a power of two
+// 2^a with p + 1 = (2q + 1) 2^a give the q-th chunk of the a-th octave from the
+// top, (P / 2^(a+1), P / 2^a] counted from 1.  There are as many odd multiples of
+// 2^a up to P as chunks in that octave, so each chunk is taken once; the q-th of
+// an octave is half the 2q-th of the octave above and sits beside it.
+__device__ __forceinline__ int fold_chunk(int p, int P)
 {
-    const int64_t r0 = (int64_t)blockIdx.x * kHarmCols + threadIdx.x;
-    const int c = (K - 1) / 2;
-    const int krow = blockIdx.y;                       // row of the fold
-    const int dk = krow - (KH - 1) / 2;                // k - c of the fundamental
-    float s[kHarmPerLane];
-    bool in[kHarmPerLane];
+    const int a = __builtin_ctz((unsigned)(p + 1));
+    return (int)((uint32_t)P >> (a + 1)) + ((p + 1) >> (a + 1));
+}
+
+// Work item l of [0, P rows): a chunk (place p in the octave order) and a row.
+// Consecutive workgroups go to the 8 XCDs in turn, each with an L2 of its own, so
+// the items are dealt out in runs of kFoldRun places x all rows per XCD: the
+// waves that share lines share an L2.
+constexpr int kFoldRun = 32, kXcds = 8;
+
+__device__ __forceinline__ void fold_item(int64_t l, int P, int rows, int& p, int& row)
+{
+    const int run = P >= kXcds * kFoldRun ? kFoldRun : P / kXcds;
+    const int dealt = run > 0 ? P / (kXcds * run) * (kXcds * run) : 0;   // places in full rounds
+    if (l >= (int64_t)dealt * rows) {
+        const uint32_t i = (uint32_t)(l - (int64_t)dealt * rows);    // < 2^20
+        const uint32_t q = i / (uint32_t)rows;
+        p = dealt + (int)q;
+        row = (int)(i - q * (uint32_t)rows);
+        return;
+    }
+    const uint32_t span = (uint32_t)(kXcds * run) * (uint32_t)rows;   // < 2^20
+    const int64_t round = l >> 32 ? l / span : (int64_t)((uint32_t)l / span);
+    const uint32_t j = (uint32_t)(l - round * span);
+    const uint32_t x = j % kXcds, i = j / kXcds;
+    const uint32_t q = i / (uint32_t)rows;
+    p = (int)((round * kXcds + x) * run + q);
+    row = (int)(i - q * (uint32_t)rows);
+}
+
+// Adds harmonics H/2 + 1 .. H of columns r + 64 j to s, in that order (FULL:
+// all of them lie below NH).  Harmonic h is at h (dk N + r) from the centre row.
+template <int H, bool FULL>
+__device__ __forceinline__ void fold_add(const float* __restrict__ centre, int64_t N, int64_t dk,
+                                         int64_t r, int64_t NH, float (&s)[kFoldPerLane])
+{
+    constexpr int FIRST = H == 1 ? 1 : H / 2 + 1;
+    constexpr int COUNT = H == 1 ? 1 : H / 2;
+    constexpr int GROUP = COUNT < kFoldGroup ? COUNT : kFoldGroup;
 #pragma unroll
-    for (int j = 0; j < kHarmPerLane; ++j) {
-        in[j] = r0 + (int64_t)j * kHarmThreads < NH;
+    for (int g = 0; g < COUNT; g += GROUP) {
+        float v[GROUP][kFoldPerLane];
+#pragma unroll
+        for (int i = 0; i < GROUP; ++i) {
+            const int h = FIRST + g + i;
+            const float* row = centre + h * (dk * N + r);
+#pragma unroll
+            for (int j = 0; j < kFoldPerLane; ++j)
+                v[i][j] = FULL || r + j * kFoldThreads < NH ? row[h * j * kFoldThreads] : 0.f;
+        }
+#pragma unroll
+        for (int i = 0; i < GROUP; ++i)
+#pragma unroll
+            for (int j = 0; j < kFoldPerLane; ++j)
+                s[j] += v[i][j];
+    }
+}
+
+__device__ __forceinline__ void fold_put(float* __restrict__ o, int64_t r, int64_t NH,
+                                         const float (&s)[kFoldPerLane])
+{
+#pragma unroll
+    for (int j = 0; j < kFoldPerLane; ++j)
+        if (r + j * kFoldThreads < NH)
+            o[j * kFoldThreads] = s[j];
+}
+
+// One stage of a wave's chain: if (dk, r) lies in fold H's domain, add its new
+// harmonics and store the sums where the fold is wanted; false ends the chain.
+template <int LOG>
+__device__ __forceinline__ bool fold_stage(const float* __restrict__ centre, int64_t N, int c,
+                                           int64_t dk, int64_t r0, int64_t r, const FoldOut& out,
+                                           float (&s)[kFoldPerLane])
+{
+    constexpr int H = 1 << LOG;
+    const int kc = c / H;
+    const int64_t NH = (N + H - 1) / H;
+    if (dk > kc || -dk > kc || r0 >= NH)
+        return false;                 // uniform in the wave
+    if (r0 + kFoldCols <= NH)
+        fold_add<H, true>(centre, N, dk, r, NH, s);
+    else
+        fold_add<H, false>(centre, N, dk, r, NH, s);
+    if (out.p[LOG] != nullptr)
+        fold_put(out.p[LOG] + (dk + kc) * NH + r, r, NH, s);
+    return true;
+}
+
+// The chain of one wave at row offset dk and columns r0 + t + 64 j: folds 2^log_first
+// .. 2^log_last, from prev (the fold below the first) or, without it, from the
+// plane itself.
+__device__ __forceinline__ void fold_chain(const float* __restrict__ plane, int64_t N, int c,
+                                           int64_t dk, int64_t r0, int t,
+                                           const float* __restrict__ prev, int log_first,
+                                           int log_last, const FoldOut& out)
+{
+    const float* centre = plane + (int64_t)c * N;
+    const int64_t r = r0 + t;
+    float s[kFoldPerLane];
+#pragma unroll
+    for (int j = 0; j < kFoldPerLane; ++j)
         s[j] = 0.f;
-    }
-    int h0 = 1;
+    int log = 0;
     if (prev != nullptr) {
-        const float* p = prev + (int64_t)(dk + (KHp - 1) / 2) * NHp + r0;
+        const int Hp = 1 << (log_first - 1);
+        const int64_t NHp = (N + Hp - 1) / Hp;
+        const float* p = prev + (dk + c / Hp) * NHp + r;
 #pragma unroll
-        for (int j = 0; j < kHarmPerLane; ++j)
-            if (in[j])
-                s[j] = p[(int64_t)j * kHarmThreads];
-        h0 = H / 2 + 1;
+        for (int j = 0; j < kFoldPerLane; ++j)
+            if (r + j * kFoldThreads < NHp)
+                s[j] = p[j * kFoldThreads];
+        log = log_first;
     }
-    for (int h = h0; h <= H; ++h) {
-        const float* row = plane + (int64_t)(c + h * dk) * N + (int64_t)h * r0;
-#pragma unroll
-        for (int j = 0; j < kHarmPerLane; ++j)
-            if (in[j])
-                s[j] += row[(int64_t)h * j * kHarmThreads];
-    }
-    float* o = out + (int64_t)krow * NH + r0;
-#pragma unroll
-    for (int j = 0; j < kHarmPerLane; ++j)
-        if (in[j])
-            o[(int64_t)j * kHarmThreads] = s[j];
+    if (log <= 0 && !fold_stage<0>(centre, N, c, dk, r0, r, out, s)) return;
+    if (log <= 1 && (log_last < 1 || !fold_stage<1>(centre, N, c, dk, r0, r, out, s))) return;
+    if (log <= 2 && (log_last < 2 || !fold_stage<2>(centre, N, c, dk, r0, r, out, s))) return;
+    if (log <= 3 && (log_last < 3 || !fold_stage<3>(centre, N, c, dk, r0, r, out, s))) return;
+    if (log <= 4 && (log_last < 4 || !fold_stage<4>(centre, N, c, dk, r0, r, out, s))) return;
+    if (log <= 5 && (log_last < 5 || !fold_stage<5>(centre, N, c, dk, r0, r, out, s))) return;
+    if (log <= 6 && log_last >= 6)
+        fold_stage<6>(centre, N, c, dk, r0, r, out, s);
+}
+
+// One wave per (chunk, row of the first fold): workgroup b takes row b mod KH
+// of the (b / KH)-th chunk of the octave order.
+__global__ __launch_bounds__(kFoldThreads, 8) void fold_chain_kernel(
+    const float* __restrict__ plane, int64_t N, int K, const float* __restrict__ prev,
+    int log_first, int log_last, FoldOut out, int P, int KH)
+{
+    const int64_t b = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
+    if (b >= (int64_t)P * KH)
+        return;
+    int p, row;
+    fold_item(b, P, KH, p, row);
+    const int64_t dk = row - (KH - 1) / 2;
+    fold_chain(plane, N, (K - 1) / 2, dk, (int64_t)fold_chunk(P - 1 - p, P) * kFoldCols,
+               threadIdx.x, prev, log_first, log_last, out);
 }
 
 __global__ void zero_count_kernel(unsigned* __restrict__ count)
@@ -124,7 +254,6 @@ __global__ __launch_bounds__(kHarmThreads) void candidates_kernel(
 
 // fold column prefix sums over the spectra: colpre[b] = sum_{b' < b}
 // ceil(N_b' / H), and the same for H/2 in prevpre (one workgroup).
-constexpr int kHScanThreads = 256;
 
 __global__ __launch_bounds__(kHScanThreads) void harmonic_scan_kernel(
     const int64_t* __restrict__ offsets, int nspec, int H, int64_t* __restrict__ colpre,
@@ -185,6 +314,85 @@ __device__ __forceinline__ int column_spectrum(const int64_t* __restrict__ colpr
             hi = mid - 1;
     }
     return lo;
+}
+
+// Batched chains.  Work item = (spectrum, chunk of the octave order, row of
+// fold 2), numbered in that order.
+__host__ __device__ inline int fold2_rows(int K) { return 2 * ((K - 1) / 2 / 2) + 1; }
+
+__host__ __device__ inline int64_t fold2_chunks(int64_t N)
+{
+    return ((N + 1) / 2 + kFoldCols - 1) / kFoldCols;
+}
+
+// Prefix sums over the spectra, one workgroup each: row 0 of pre[.][nspec + 1]
+// counts the work items, row i the columns of fold 2^i.
+__global__ __launch_bounds__(kHScanThreads) void fold_scan_kernel(
+    const int64_t* __restrict__ offsets, int nspec, int rows, int64_t* __restrict__ pre)
+{
+    __shared__ int64_t part[kHScanThreads];
+    __shared__ int64_t carry;
+    const int t = threadIdx.x;
+    const int i = blockIdx.x;
+    int64_t* const out = pre + (int64_t)i * (nspec + 1);
+    if (t == 0) {
+        carry = 0;
+        out[0] = 0;
+    }
+    __syncthreads();
+    for (int base = 0; base < nspec; base += kHScanThreads) {
+        const int b = base + t;
+        int64_t v = 0;
+        if (b < nspec) {
+            const int64_t n = offsets[b + 1] - offsets[b];
+            if (n > 0)
+                v = i == 0 ? fold2_chunks(n) * rows : (n + (1 << i) - 1) >> i;
+        }
+        part[t] = v;
+        __syncthreads();
+        for (int d = 1; d < kHScanThreads; d <<= 1) {
+            const int64_t x = t >= d ? part[t - d] : 0;
+            __syncthreads();
+            part[t] += x;
+            __syncthreads();
+        }
+        if (b < nspec)
+            out[b + 1] = carry + part[t];
+        __syncthreads();
+        if (t == kHScanThreads - 1)
+            carry += part[t];
+        __syncthreads();
+    }
+}
+
+// One wave per work item (more waves than the host's bound on them stride on),
+// so the waves of the moment work on neighbouring chunks of one spectrum.  Fold
+// 2^i of spectrum b lies at out.p[i] + KH pre[i][b].  Measured, 8 spectra of
+// 131073 bins, 41 rows, folds 2..16: 51 us; 64 us as one launch per fold, and
+// 83 us with persistent waves, which paid for a new spectrum nearly every item.
+__global__ __launch_bounds__(kFoldThreads, 8) void fold_chain_batched_kernel(
+    const float* __restrict__ planes, const int64_t* __restrict__ offsets, int nspec, int K,
+    int log_last, FoldOut out, const int64_t* __restrict__ pre)
+{
+    const int c = (K - 1) / 2, kc = c / 2;
+    const int rows = fold2_rows(K);
+    const int64_t total = pre[nspec];
+    for (int64_t g = (int64_t)blockIdx.y * gridDim.x + blockIdx.x; g < total;
+         g += (int64_t)gridDim.x * gridDim.y) {
+        const int b = column_spectrum(pre, nspec, g);
+        const int64_t off = offsets[b], N = offsets[b + 1] - off;
+        FoldOut o = {};
+#pragma unroll
+        for (int i = 1; i < kMaxFolds; ++i)
+            if (i <= log_last)
+                o.p[i] = out.p[i] + (int64_t)(2 * (c >> i) + 1) * pre[(int64_t)i * (nspec + 1) + b];
+        const int P = (int)fold2_chunks(N);
+        int p, row;
+        fold_item(g - pre[b], P, rows, p, row);
+        fold_chain(planes + (int64_t)K * off, N, c, row - kc,
+                   (int64_t)fold_chunk(P - 1 - p, P) * kFoldCols, threadIdx.x, nullptr, 1,
+                   log_last, o);
+    }
 }
 
 // Persistent grid: each lane takes fold columns g (stride gridDim.x x
@@ -286,20 +494,34 @@ void harmonic_shape(int64_t N, int K, int H, int* KH, int64_t* NH)
     *NH = (N + H - 1) / H;
 }
 
+// Folds 2^log_first .. 2^log_last (those with an output pointer), on top of prev
+// if given.
+hipError_t launch_fold_chain(const float* plane, int64_t N, int K, const float* prev,
+                             int log_first, int log_last, float* const* sums, hipStream_t s)
+{
+    int KH = 0;
+    int64_t NH = 0;
+    harmonic_shape(N, K, 1 << log_first, &KH, &NH);
+    if (NH == 0)
+        return hipSuccess;
+    const int64_t P = (NH + kFoldCols - 1) / kFoldCols;
+    FoldOut out = {};
+    for (int i = log_first; i <= log_last; ++i)
+        out.p[i] = sums[i - log_first];
+    const int64_t waves = P * KH, gx = waves < kMaxFoldGridX ? waves : kMaxFoldGridX;
+    hipLaunchKernelGGL(fold_chain_kernel,
+                       dim3((unsigned)gx, (unsigned)((waves + gx - 1) / gx)), dim3(kFoldThreads),
+                       0, s, plane, N, K, prev, log_first, log_last, out, (int)P, KH);
+    return hipGetLastError();
+}
+
 hipError_t launch_harmonic_sum(const float* plane, int64_t N, int K, int H, const float* prev,
                                float* out, hipStream_t s)
 {
-    int KH = 0, KHp = 0;
-    int64_t NH = 0, NHp = 0;
-    harmonic_shape(N, K, H, &KH, &NH);
-    if (prev != nullptr)
-        harmonic_shape(N, K, H / 2, &KHp, &NHp);
-    if (NH == 0)
-        return hipSuccess;
-    const dim3 grid((unsigned)((NH + kHarmCols - 1) / kHarmCols), (unsigned)KH);
-    hipLaunchKernelGGL(harmonic_sum_kernel, grid, dim3(kHarmThreads), 0, s, plane, N, K, H, prev,
-                       NHp, KHp, out, NH, KH);
-    return hipGetLastError();
+    int log = 0;
+    while ((1 << log) < H)
+        ++log;
+    return launch_fold_chain(plane, N, K, prev, log, log, &out, s);
 }
 
 hipError_t launch_candidates(const float* S, int64_t N, int K, int H, float threshold,
@@ -335,6 +557,28 @@ hipError_t launch_harmonic_batched(const float* planes, const int64_t* offsets, 
         return e;
     hipLaunchKernelGGL(harmonic_batched_kernel, dim3(kHarmBatchedGrid), dim3(kHarmThreads), 0, s,
                        planes, offsets, nspec, K, H, prev, KHp, colpre, prevpre, sums, KH);
+    return hipGetLastError();
+}
+
+hipError_t launch_fold_chain_batched(const float* planes, const int64_t* offsets, int nspec,
+                                     int64_t capacity, int K, int log_last, float* const* sums,
+                                     int64_t* pre, hipStream_t s)
+{
+    hipLaunchKernelGGL(fold_scan_kernel, dim3((unsigned)(log_last + 1)), dim3(kHScanThreads), 0, s,
+                       offsets, nspec, fold2_rows(K), pre);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess)
+        return e;
+    FoldOut out = {};
+    for (int i = 1; i <= log_last; ++i)
+        out.p[i] = sums[i - 1];
+    // sum_b chunks(N_b) <= capacity / (2 kFoldCols) + 2 nspec
+    const int64_t waves = (capacity / (2 * kFoldCols) + 2 * (int64_t)nspec) * fold2_rows(K);
+    const int64_t gx = waves < kMaxFoldGridX ? waves : kMaxFoldGridX;
+    const int64_t gy = (waves + gx - 1) / gx;
+    hipLaunchKernelGGL(fold_chain_batched_kernel,
+                       dim3((unsigned)gx, (unsigned)(gy < kMaxFoldGridY ? gy : kMaxFoldGridY)),
+                       dim3(kFoldThreads), 0, s, planes, offsets, nspec, K, log_last, out, pre);
     return hipGetLastError();
 }
 

@@ -96,6 +96,15 @@ hipError_t launch_r2c_batched(const float* x, int log2n, int nseries, float scal
 void harmonic_shape(int64_t N, int K, int H, int* KH, int64_t* NH);
 hipError_t launch_harmonic_sum(const float* plane, int64_t N, int K, int H, const float* prev,
                                float* out, hipStream_t s);
+// Folds 2^log_first .. 2^log_last in one launch, into sums[0 ..] (one pointer
+// per fold), on top of prev (the fold below the first) if given.
+hipError_t launch_fold_chain(const float* plane, int64_t N, int K, const float* prev,
+                             int log_first, int log_last, float* const* sums, hipStream_t s);
+// Folds 2 .. 2^log_last of every spectrum of a batch of at most `capacity` bins;
+// pre holds (log_last + 1) (nspec + 1) int64.
+hipError_t launch_fold_chain_batched(const float* planes, const int64_t* offsets, int nspec,
+                                     int64_t capacity, int K, int log_last, float* const* sums,
+                                     int64_t* pre, hipStream_t s);
 hipError_t launch_candidates(const float* S, int64_t N, int K, int H, float threshold,
                              fdas_candidate* out, int capacity, unsigned* count, hipStream_t s);
 // Batched folds / candidates over the planes of fdas_correlate_batched;

@@ -1001,10 +1001,9 @@ int fdas_find_candidates_batched(const float* sums_dev, const int64_t* offsets_d
                                                      capacity, count_dev, stream);
         return e == hipSuccess ? ok() : hip_fail(e, "candidates launch");
     }
-    auto* pre = static_cast<int64_t*>(ws_dev);
     const hipError_t e = fdas::launch_candidates_batched(sums_dev, offsets_dev, nspec, K, H,
                                                          threshold, out_dev, capacity, count_dev,
-                                                         pre, pre + nspec + 1, stream);
+                                                         static_cast<int64_t*>(ws_dev), stream);
     if (e != hipSuccess)
         return hip_fail(e, "batched candidates launch");
     return ok();

@@ -213,18 +213,10 @@ __global__ void zero_count_kernel(unsigned* __restrict__ count)
         *count = 0u;
 }
 
-// Peaks of one fold: S > threshold and S >= each neighbour inside the fold.
-__global__ __launch_bounds__(kHarmThreads) void candidates_kernel(
-    const float* __restrict__ S, int64_t NH, int KH, float threshold, int row0,
-    fdas_candidate* __restrict__ out, int capacity, unsigned* __restrict__ count)
+// Whether v = S[k][r] is >= each of its neighbours inside the fold.
+__device__ __forceinline__ bool is_peak(const float* __restrict__ S, int64_t NH, int KH, int k,
+                                        int64_t r, float v)
 {
-    const int64_t r = (int64_t)blockIdx.x * kHarmThreads + threadIdx.x;
-    const int k = blockIdx.y;
-    if (r >= NH)
-        return;
-    const float v = S[(int64_t)k * NH + r];
-    if (!(v > threshold))
-        return;
     bool peak = true;
     for (int a = -1; a <= 1; ++a) {
         const int kk = k + a;
@@ -237,16 +229,68 @@ __global__ __launch_bounds__(kHarmThreads) void candidates_kernel(
             peak = peak && v >= S[(int64_t)kk * NH + rr];
         }
     }
-    if (!peak)
-        return;
+    return peak;
+}
+
+__device__ __forceinline__ void put_candidate(fdas_candidate* __restrict__ out, int capacity,
+                                              unsigned* __restrict__ count, int64_t r, int row,
+                                              float power)
+{
     const unsigned slot = atomicAdd(count, 1u);
     if (slot < (unsigned)capacity) {
         fdas_candidate cand;
         cand.r = r;
-        cand.row = row0 + k;
-        cand.power = v;
+        cand.row = row;
+        cand.power = power;
         out[slot] = cand;
     }
+}
+
+// Peaks of one fold: S > threshold and S >= each neighbour inside the fold.
+// Bound by reading the fold once; a lane keeps kCandPerLane loads in flight
+// (lane t takes columns t + kHarmThreads j), which is what the rate hangs on:
+// 57 us for 85 x 2^20 (6.3 TB/s), 107 us with one.
+constexpr int kCandPerLane = 8;
+constexpr int kCandCols = kHarmThreads * kCandPerLane;
+
+// Columns c0 .. c0 + kCandCols of row k of one fold; a candidate's r is reported
+// from column r_at on.
+__device__ __forceinline__ void find_peaks(const float* __restrict__ S, int64_t NH, int KH, int k,
+                                           int64_t c0, float threshold, int row0, int64_t r_at,
+                                           fdas_candidate* __restrict__ out, int capacity,
+                                           unsigned* __restrict__ count)
+{
+    const int64_t r = c0 + threadIdx.x;
+    const float* row = S + (int64_t)k * NH + r;
+    float v[kCandPerLane];
+    if (c0 + kCandCols <= NH) {
+#pragma unroll
+        for (int j = 0; j < kCandPerLane; ++j)
+            v[j] = row[j * kHarmThreads];
+    } else {
+        // a column outside the fold gets the threshold itself: no candidate
+#pragma unroll
+        for (int j = 0; j < kCandPerLane; ++j)
+            v[j] = r + j * kHarmThreads < NH ? row[j * kHarmThreads] : threshold;
+    }
+    bool any = false;
+#pragma unroll
+    for (int j = 0; j < kCandPerLane; ++j)
+        any = any || v[j] > threshold;
+    if (!any)
+        return;
+#pragma unroll
+    for (int j = 0; j < kCandPerLane; ++j)
+        if (v[j] > threshold && is_peak(S, NH, KH, k, r + j * kHarmThreads, v[j]))
+            put_candidate(out, capacity, count, r_at + r + j * kHarmThreads, row0 + k, v[j]);
+}
+
+__global__ __launch_bounds__(kHarmThreads) void candidates_kernel(
+    const float* __restrict__ S, int64_t NH, int KH, float threshold, int row0,
+    fdas_candidate* __restrict__ out, int capacity, unsigned* __restrict__ count)
+{
+    find_peaks(S, NH, KH, blockIdx.y, (int64_t)blockIdx.x * kCandCols, threshold, row0, 0, out,
+               capacity, count);
 }
 
 // ---- batched: the planes of fdas_correlate_batched (plane b at K offsets[b],
@@ -320,15 +364,17 @@ __device__ __forceinline__ int column_spectrum(const int64_t* __restrict__ colpr
 // fold 2), numbered in that order.
 __host__ __device__ inline int fold2_rows(int K) { return 2 * ((K - 1) / 2 / 2) + 1; }
 
-__host__ __device__ inline int64_t fold2_chunks(int64_t N)
+__device__ __forceinline__ int64_t fold_columns(int64_t N, int log)
 {
-    return ((N + 1) / 2 + kFoldCols - 1) / kFoldCols;
+    return (N + (1 << log) - 1) >> log;
 }
 
 // Prefix sums over the spectra, one workgroup each: row 0 of pre[.][nspec + 1]
-// counts the work items, row i the columns of fold 2^i.
+// counts the work items (fold 2^log in chunks of `cols` columns, times `rows`),
+// row i the columns of fold 2^(log + i - 1).  `zero` (or NULL) is set to 0.
 __global__ __launch_bounds__(kHScanThreads) void fold_scan_kernel(
-    const int64_t* __restrict__ offsets, int nspec, int rows, int64_t* __restrict__ pre)
+    const int64_t* __restrict__ offsets, int nspec, int log, int cols, int rows,
+    int64_t* __restrict__ pre, unsigned* __restrict__ zero)
 {
     __shared__ int64_t part[kHScanThreads];
     __shared__ int64_t carry;
@@ -338,6 +384,8 @@ __global__ __launch_bounds__(kHScanThreads) void fold_scan_kernel(
     if (t == 0) {
         carry = 0;
         out[0] = 0;
+        if (i == 0 && zero != nullptr)
+            *zero = 0u;
     }
     __syncthreads();
     for (int base = 0; base < nspec; base += kHScanThreads) {
@@ -346,7 +394,8 @@ __global__ __launch_bounds__(kHScanThreads) void fold_scan_kernel(
         if (b < nspec) {
             const int64_t n = offsets[b + 1] - offsets[b];
             if (n > 0)
-                v = i == 0 ? fold2_chunks(n) * rows : (n + (1 << i) - 1) >> i;
+                v = i == 0 ? (fold_columns(n, log) + cols - 1) / cols * rows
+                           : fold_columns(n, log + i - 1);
         }
         part[t] = v;
         __syncthreads();
@@ -386,7 +435,7 @@ __global__ __launch_bounds__(kFoldThreads, 8) void fold_chain_batched_kernel(
         for (int i = 1; i < kMaxFolds; ++i)
             if (i <= log_last)
                 o.p[i] = out.p[i] + (int64_t)(2 * (c >> i) + 1) * pre[(int64_t)i * (nspec + 1) + b];
-        const int P = (int)fold2_chunks(N);
+        const int P = (int)((fold_columns(N, 1) + kFoldCols - 1) / kFoldCols);
         int p, row;
         fold_item(g - pre[b], P, rows, p, row);
         fold_chain(planes + (int64_t)K * off, N, c, row - kc,
@@ -433,48 +482,22 @@ __global__ __launch_bounds__(kHarmThreads) void harmonic_batched_kernel(
     }
 }
 
-// Peaks of every spectrum's fold; the record's r is the packed bin index
-// offsets[b] + r, which names the spectrum too.
+// Peaks of every spectrum's fold H = 2^log; the record's r is the packed bin
+// index offsets[b] + r, which names the spectrum too.  Workgroup row y takes fold
+// row y, its workgroups stride over the chunks of kCandCols columns that pre row 0
+// counts (a spectrum found per chunk; one found per column and lane took 67 us for
+// 8 x 41 x 131073, this 28 us).
 __global__ __launch_bounds__(kHarmThreads) void candidates_batched_kernel(
-    const float* __restrict__ sums, const int64_t* __restrict__ offsets, int nspec, int H,
-    const int64_t* __restrict__ colpre, int KH, float threshold, int row0,
+    const float* __restrict__ sums, const int64_t* __restrict__ offsets, int nspec, int log,
+    const int64_t* __restrict__ pre, int KH, float threshold, int row0,
     fdas_candidate* __restrict__ out, int capacity, unsigned* __restrict__ count)
 {
-    const int64_t total = colpre[nspec];
-    for (int64_t g = (int64_t)blockIdx.x * kHarmThreads + threadIdx.x; g < total;
-         g += (int64_t)gridDim.x * kHarmThreads) {
-        const int b = column_spectrum(colpre, nspec, g);
-        const int64_t Nb = offsets[b + 1] - offsets[b];
-        const int64_t NH = (Nb + H - 1) / H;
-        const int64_t r = g - colpre[b];
-        const float* S = sums + (int64_t)KH * colpre[b];
-        for (int k = 0; k < KH; ++k) {
-            const float v = S[(int64_t)k * NH + r];
-            if (!(v > threshold))
-                continue;
-            bool peak = true;
-            for (int a = -1; a <= 1; ++a) {
-                const int kk = k + a;
-                if (kk < 0 || kk >= KH)
-                    continue;
-                for (int d = -1; d <= 1; ++d) {
-                    const int64_t rr = r + d;
-                    if ((a == 0 && d == 0) || rr < 0 || rr >= NH)
-                        continue;
-                    peak = peak && v >= S[(int64_t)kk * NH + rr];
-                }
-            }
-            if (!peak)
-                continue;
-            const unsigned slot = atomicAdd(count, 1u);
-            if (slot < (unsigned)capacity) {
-                fdas_candidate cand;
-                cand.r = offsets[b] + r;
-                cand.row = row0 + k;
-                cand.power = v;
-                out[slot] = cand;
-            }
-        }
+    const int64_t total = pre[nspec];
+    for (int64_t g = blockIdx.x; g < total; g += gridDim.x) {
+        const int b = column_spectrum(pre, nspec, g);
+        const int64_t off = offsets[b], NH = fold_columns(offsets[b + 1] - off, log);
+        find_peaks(sums + (int64_t)KH * pre[nspec + 1 + b], NH, KH, blockIdx.y,
+                   (g - pre[b]) * kCandCols, threshold, row0, off, out, capacity, count);
     }
 }
 
@@ -484,6 +507,7 @@ __global__ __launch_bounds__(kHarmThreads) void candidates_batched_kernel(
 #define FDAS_HARM_BATCHED_GRID 2048
 #endif
 constexpr int kHarmBatchedGrid = FDAS_HARM_BATCHED_GRID;
+constexpr int kCandBatchedGrid = FDAS_HARM_BATCHED_GRID < 512 ? FDAS_HARM_BATCHED_GRID : 512;
 
 }  // namespace
 
@@ -535,7 +559,7 @@ hipError_t launch_candidates(const float* S, int64_t N, int K, int H, float thre
     if (e != hipSuccess || NH == 0)
         return e;
     const int row0 = (K - 1) / 2 - (KH - 1) / 2;
-    const dim3 grid((unsigned)((NH + kHarmThreads - 1) / kHarmThreads), (unsigned)KH);
+    const dim3 grid((unsigned)((NH + kCandCols - 1) / kCandCols), (unsigned)KH);
     hipLaunchKernelGGL(candidates_kernel, grid, dim3(kHarmThreads), 0, s, S, NH, KH, threshold,
                        row0, out, capacity, count);
     return hipGetLastError();
@@ -565,7 +589,7 @@ hipError_t launch_fold_chain_batched(const float* planes, const int64_t* offsets
                                      int64_t* pre, hipStream_t s)
 {
     hipLaunchKernelGGL(fold_scan_kernel, dim3((unsigned)(log_last + 1)), dim3(kHScanThreads), 0, s,
-                       offsets, nspec, fold2_rows(K), pre);
+                       offsets, nspec, 1, kFoldCols, fold2_rows(K), pre, (unsigned*)nullptr);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess)
         return e;
@@ -584,24 +608,23 @@ hipError_t launch_fold_chain_batched(const float* planes, const int64_t* offsets
 
 hipError_t launch_candidates_batched(const float* sums, const int64_t* offsets, int nspec, int K,
                                      int H, float threshold, fdas_candidate* out, int capacity,
-                                     unsigned* count, int64_t* colpre, int64_t* prevpre,
-                                     hipStream_t s)
+                                     unsigned* count, int64_t* pre, hipStream_t s)
 {
     int KH = 0;
     int64_t NH = 0;
     harmonic_shape(1, K, H, &KH, &NH);
-    hipLaunchKernelGGL(zero_count_kernel, dim3(1), dim3(64), 0, s, count);
+    int log = 0;
+    while ((1 << log) < H)
+        ++log;
+    hipLaunchKernelGGL(fold_scan_kernel, dim3(2), dim3(kHScanThreads), 0, s, offsets, nspec, log,
+                       kCandCols, 1, pre, count);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess)
         return e;
-    hipLaunchKernelGGL(harmonic_scan_kernel, dim3(1), dim3(kHScanThreads), 0, s, offsets, nspec, H,
-                       colpre, prevpre);
-    if ((e = hipGetLastError()) != hipSuccess)
-        return e;
     const int row0 = (K - 1) / 2 - (KH - 1) / 2;
-    hipLaunchKernelGGL(candidates_batched_kernel, dim3(kHarmBatchedGrid), dim3(kHarmThreads), 0,
-                       s, sums, offsets, nspec, H, colpre, KH, threshold, row0, out, capacity,
-                       count);
+    hipLaunchKernelGGL(candidates_batched_kernel, dim3(kCandBatchedGrid, (unsigned)KH),
+                       dim3(kHarmThreads), 0, s, sums, offsets, nspec, log, pre, KH, threshold,
+                       row0, out, capacity, count);
     return hipGetLastError();
 }
 

@@ -109,14 +109,13 @@ hipError_t launch_candidates(const float* S, int64_t N, int K, int H, float thre
                              fdas_candidate* out, int capacity, unsigned* count, hipStream_t s);
 // Batched folds / candidates over the planes of fdas_correlate_batched;
 // colpre and prevpre ([nspec + 1] int64 each) hold the fold column prefix
-// sums for H and H/2.
+// sums for H and H/2; the candidates' pre holds 2 (nspec + 1) int64.
 hipError_t launch_harmonic_batched(const float* planes, const int64_t* offsets, int nspec, int K,
                                    int H, const float* prev, float* sums, int64_t* colpre,
                                    int64_t* prevpre, hipStream_t s);
 hipError_t launch_candidates_batched(const float* sums, const int64_t* offsets, int nspec, int K,
                                      int H, float threshold, fdas_candidate* out, int capacity,
-                                     unsigned* count, int64_t* colpre, int64_t* prevpre,
-                                     hipStream_t s);
+                                     unsigned* count, int64_t* pre, hipStream_t s);
 
 // Streaming probes: n floats written with `value`, or read and summed into
 // sums[FDAS_STREAM_PARTIALS] (one partial per workgroup).

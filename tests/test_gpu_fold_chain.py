@@ -47,3 +47,23 @@ def test_fold_chain_batched(fd, K, lens):
     for i, S in enumerate(folds[1:], 1):
         ref = np.concatenate([oh.harmonic_sum(p, 1 << i).reshape(-1) for p in planes])
         assert np.array_equal(S.cpu().numpy()[:ref.size], ref), 1 << i
+
+
+@pytest.mark.parametrize("N", [1, 2047, 2048, 2049, 4097])
+def test_candidates_at_chunk_edges(fd, N):
+    # lengths around the 2048 columns of a workgroup, negative powers and a
+    # threshold of -inf included (every finite local maximum), one NaN
+    import torch
+    K = 3
+    P = syn.random_plane(N, K, N) - np.float32(0.5)
+    if N > 2:
+        P[1, N // 2] = np.nan
+    want = sorted(map(tuple, oh.peaks(P, -np.inf).tolist()))
+    r, row, power, n = fd.candidates(torch.from_numpy(P).cuda(), N, K, 1, -np.inf, capacity=1 << 16)
+    assert n == len(want) > 0 and sorted(zip(row.tolist(), r.tolist())) == want
+    offs = torch.tensor([0, N, 2 * N], device="cuda")
+    flat = torch.from_numpy(np.concatenate([P.reshape(-1)] * 2)).cuda()
+    spec, r, row, power, n = fd.candidates_batched(flat, offs, K, 1, -np.inf, capacity=1 << 16)
+    assert n == 2 * len(want)
+    for b in (0, 1):
+        assert sorted(zip(row[spec == b].tolist(), r[spec == b].tolist())) == want

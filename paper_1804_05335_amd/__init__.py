@@ -214,21 +214,59 @@ def harmonic_sums(plane, max_fold: int):
     return folds
 
 
+# fdas_candidate as numpy reads it, and the records of each list that travel
+# with the counts (longer lists are fetched in a second transfer)
+_RECORD = [("r", "<i8"), ("row", "<i4"), ("power", "<f4")]
+_FIRST_RECORDS = 512
+
+
+class _CandidateLists:
+    """Candidate lists of several folds: device buffers filled by ``find``
+    calls, read back together by ``read``."""
+
+    def __init__(self, lists: int, capacity: int, device):
+        import torch
+        self.capacity = capacity
+        self.out = [torch.empty(max(capacity, 1) * 16, dtype=torch.uint8, device=device)
+                    for _ in range(lists)]
+        self.counts = torch.empty(max(lists, 1), dtype=torch.int32, device=device)
+
+    def count(self, i: int):
+        return self.counts[i:i + 1]
+
+    def read(self):
+        """[(records, count)] of every list, in one transfer with one wait
+        (one more for each list of over _FIRST_RECORDS)."""
+        import numpy as np
+        import torch
+        first = 16 * min(self.capacity, _FIRST_RECORDS)
+        host = torch.cat([self.counts.view(torch.uint8)] + [o[:first] for o in self.out])
+        host = host.cpu().numpy()
+        found = []
+        at = 4 * self.counts.numel()
+        for i, o in enumerate(self.out):
+            n = int(host[4 * i:4 * i + 4].view(np.uint32)[0])
+            keep = 16 * min(n, self.capacity)
+            rec = host[at:at + min(keep, first)] if keep <= first else o[:keep].cpu().numpy()
+            found.append((rec.view(np.dtype(_RECORD)), n))
+            at += first
+        return found
+
+
+def _by_row(found):
+    import numpy as np
+    rec, n = found
+    rec = rec[np.lexsort((rec["r"], rec["row"]))]
+    return rec["r"].copy(), rec["row"].copy(), rec["power"].copy(), n
+
+
 def candidates(sums, N: int, K: int, H: int, threshold: float, capacity: int = 1 << 16):
     """Peaks of one fold above `threshold` (Sec. 3): (r int64, row int32,
     power float32) host arrays sorted by (row, r), and the total count
     (which may exceed `capacity`; then only `capacity` are returned)."""
-    import numpy as np
-    import torch
-    out = torch.empty(max(capacity, 1) * 16, dtype=torch.uint8, device=sums.device)
-    count = torch.zeros(1, dtype=torch.int32, device=sums.device)
-    fdas_find_candidates(sums, N, K, H, threshold, out, capacity, count)
-    n = int(count.item())
-    rec = np.frombuffer(out.cpu().numpy().tobytes(), dtype=np.dtype(
-        [("r", "<i8"), ("row", "<i4"), ("power", "<f4")]))[:min(n, capacity)]
-    order = np.lexsort((rec["r"], rec["row"]))
-    rec = rec[order]
-    return rec["r"].copy(), rec["row"].copy(), rec["power"].copy(), n
+    lists = _CandidateLists(1, capacity, sums.device)
+    fdas_find_candidates(sums, N, K, H, threshold, lists.out[0], capacity, lists.count(0))
+    return _by_row(lists.read()[0])
 
 
 def search(x, zmax: float, dz: float, M: int, L: int, max_fold: int, thresholds,
@@ -243,18 +281,18 @@ def search(x, zmax: float, dz: float, M: int, L: int, max_fold: int, thresholds,
     z = (row - (K - 1)/2) dz.  Every step runs in the library's kernels."""
     n = x.numel()
     N = n // 2
-    spec = spectrum_from_series(x, 1.0 / float(n) ** 0.5)[:N].contiguous()
+    # the templates' call waits for the stream: first, while nothing is queued
     taps, bank = make_bank(zmax, dz, M, L, device=x.device)
     K = taps.shape[0]
+    spec = spectrum_from_series(x, 1.0 / float(n) ** 0.5)[:N].contiguous()
     plane = correlate(spec, bank, K, M, L)
-    folds = harmonic_sums(plane, max_fold)
-    out = {}
-    H = 1
-    for S in folds:
-        if H in thresholds:
-            out[H] = candidates(S, N, K, H, float(thresholds[H]), capacity)
-        H *= 2
-    return out
+    folds = {1 << i: S for i, S in enumerate(harmonic_sums(plane, max_fold))}
+    wanted = [H for H in folds if H in thresholds]
+    lists = _CandidateLists(len(wanted), capacity, x.device)
+    for i, H in enumerate(wanted):
+        fdas_find_candidates(folds[H], N, K, H, float(thresholds[H]), lists.out[i], capacity,
+                             lists.count(i))
+    return {H: _by_row(found) for H, found in zip(wanted, lists.read())} if wanted else {}
 
 
 def fold_prefix(offsets_host, H: int):
@@ -270,11 +308,16 @@ def fold_prefix(offsets_host, H: int):
 def harmonic_sums_batched(planes, offsets, K: int, max_fold: int):
     """Folds 2, 4, .., max_fold of the planes of correlate_batched (flat
     float32 device tensor; offsets the int64 device tensor of nspec + 1
-    packed-bin offsets), all folds of all spectra in one launch.  Returns the list [planes, S_2, S_4, ...] of flat
+    packed-bin offsets), all folds of all spectra in one launch.  Returns
+    the list [planes, S_2, S_4, ...] of flat
     tensors; fold H of spectrum b is S_H[K_H C_H[b] : K_H C_H[b+1]] viewed
     as [K_H][ceil(N_b/H)] (see fold_prefix)."""
+    return _harmonic_sums_batched(planes, offsets, offsets.cpu().numpy(), K, max_fold)
+
+
+def _harmonic_sums_batched(planes, offsets, offs, K: int, max_fold: int):
+    """harmonic_sums_batched with the offsets' host copy ``offs``."""
     import torch
-    offs = offsets.cpu().numpy()
     nspec = len(offs) - 1
     ws = torch.empty(max(fdas_harmonic_sums_batched_workspace_bytes(nspec), 1),
                      dtype=torch.uint8, device=planes.device)
@@ -290,26 +333,29 @@ def harmonic_sums_batched(planes, offsets, K: int, max_fold: int):
     return folds
 
 
-def candidates_batched(sums, offsets, K: int, H: int, threshold: float, capacity: int = 1 << 16):
-    """Peaks above `threshold` of fold H of every spectrum: (spectrum int64,
-    r int64, row int32, power float32) host arrays sorted by (spectrum, row,
-    r), and the total count."""
+def _by_spectrum(found, offs):
+    """(spectrum, r, row, power, count) sorted by (spectrum, row, r); offs
+    the host copy of the offsets."""
     import numpy as np
-    import torch
-    nspec = offsets.numel() - 1
-    ws = torch.empty(max(fdas_harmonic_batched_workspace_bytes(nspec), 1), dtype=torch.uint8,
-                     device=sums.device)
-    out = torch.empty(max(capacity, 1) * 16, dtype=torch.uint8, device=sums.device)
-    count = torch.zeros(1, dtype=torch.int32, device=sums.device)
-    fdas_find_candidates_batched(sums, offsets, nspec, K, H, threshold, out, capacity, count, ws)
-    n = int(count.item())
-    rec = np.frombuffer(out.cpu().numpy().tobytes(), dtype=np.dtype(
-        [("r", "<i8"), ("row", "<i4"), ("power", "<f4")]))[:min(n, capacity)]
-    offs = offsets.cpu().numpy()
+    rec, n = found
     spec = np.searchsorted(offs, rec["r"], side="right") - 1
     r = rec["r"] - offs[spec]
     order = np.lexsort((r, rec["row"], spec))
     return spec[order], r[order], rec["row"][order].copy(), rec["power"][order].copy(), n
+
+
+def candidates_batched(sums, offsets, K: int, H: int, threshold: float, capacity: int = 1 << 16):
+    """Peaks above `threshold` of fold H of every spectrum: (spectrum int64,
+    r int64, row int32, power float32) host arrays sorted by (spectrum, row,
+    r), and the total count."""
+    import torch
+    nspec = offsets.numel() - 1
+    ws = torch.empty(max(fdas_harmonic_batched_workspace_bytes(nspec), 1), dtype=torch.uint8,
+                     device=sums.device)
+    lists = _CandidateLists(1, capacity, sums.device)
+    fdas_find_candidates_batched(sums, offsets, nspec, K, H, threshold, lists.out[0], capacity,
+                                 lists.count(0), ws)
+    return _by_spectrum(lists.read()[0], offsets.cpu().numpy())
 
 
 def search_batched(x, zmax: float, dz: float, M: int, L: int, max_fold: int, thresholds,
@@ -321,20 +367,26 @@ def search_batched(x, zmax: float, dz: float, M: int, L: int, max_fold: int, thr
     ``thresholds[H]``.  Each spectrum keeps its Nyquist bin (n/2 + 1 bins),
     as the batched transform packs them.  Returns {H: (series, r, row, power,
     count)} with host arrays sorted by (series, row, r)."""
+    import numpy as np
     import torch
     nseries, n = x.shape
     nb = n // 2 + 1
-    specs = spectra_from_series(x, 1.0 / float(n) ** 0.5)
-    offs = torch.arange(nseries + 1, dtype=torch.int64, device=x.device) * nb
+    offs = np.arange(nseries + 1, dtype=np.int64) * nb
+    # the templates' call waits for the stream: first, while nothing is queued
     taps, bank = make_bank(zmax, dz, M, L, device=x.device)
     K = taps.shape[0]
-    planes = correlate_batched(specs.view(-1), offs, bank, K, M, L)
-    folds = harmonic_sums_batched(planes, offs, K, max_fold)
-    out = {}
-    H = 1
-    for S in folds:
-        if H in thresholds:
-            out[H] = candidates_batched(S, offs, K, H, float(thresholds[H]), capacity)
-        H *= 2
-    return out
-
+    specs = spectra_from_series(x, 1.0 / float(n) ** 0.5)
+    offsets = torch.arange(nseries + 1, dtype=torch.int64, device=x.device) * nb
+    planes = torch.empty(K * nseries * nb, dtype=torch.float32, device=x.device)
+    correlate_batched(specs.view(-1), offsets, bank, K, M, L, planes=planes)
+    folds = {1 << i: S for i, S in
+             enumerate(_harmonic_sums_batched(planes, offsets, offs, K, max_fold))}
+    wanted = [H for H in folds if H in thresholds]
+    ws = torch.empty(max(fdas_harmonic_batched_workspace_bytes(nseries), 1), dtype=torch.uint8,
+                     device=x.device)
+    lists = _CandidateLists(len(wanted), capacity, x.device)
+    for i, H in enumerate(wanted):
+        fdas_find_candidates_batched(folds[H], offsets, nseries, K, H, float(thresholds[H]),
+                                     lists.out[i], capacity, lists.count(i), ws)
+    return {H: _by_spectrum(found, offs) for H, found in zip(wanted, lists.read())} \
+        if wanted else {}

@@ -225,6 +225,28 @@ hipError_t launch_prepare_bank(const float2* taps, int K, int M, int L, float2* 
 
 // ---- fused forward correlation ---------------------------------------------
 
+// The waves of a SIMD share its issue ports by age, so with equal work the
+// oldest workgroup of a CU runs ahead and the youngest finishes alone, with
+// nothing to fill its waits: measured on the half-bin plane of 10^6 bins (K = 85,
+// M = 256, L = 2048), the four workgroups of a CU ended at 58, 74, 87 and 100 %
+// of its time.  Every workgroup therefore starts its n-th template at priority 3 -
+// n mod 4: the one ahead gives way until the others have caught up, and they end
+// within 5 % of one another.  Measured: that plane 232 -> 217 us, the two-bin
+// plane of 300007 bins (K = 41, M = 128, L = 1024) 36.0 -> 34.6 us, the plane of
+// 2^20 bins at K = 85, M = 128, L = 512 111 -> 103 us; the plane of 2^21 bins at
+// L = 2048, where the four workgroups differ less, unchanged.
+__device__ __forceinline__ void give_way(int n)
+{
+#ifdef __HIP_DEVICE_COMPILE__   // the host pass and the CPU emulation have no priorities
+    switch (n & 3) {
+    case 0: __builtin_amdgcn_s_setprio(3); break;
+    case 1: __builtin_amdgcn_s_setprio(2); break;
+    case 2: __builtin_amdgcn_s_setprio(1); break;
+    default: __builtin_amdgcn_s_setprio(0); break;
+    }
+#endif
+}
+
 // DPP lane patterns (gfx9 wave-wide forms): lane i reads lane i + 1
 // (lane 63 reads nothing), or lane (i + 1) mod 64.
 constexpr int kDppWaveShl1 = 0x130;
@@ -306,8 +328,8 @@ struct Fwd {
         }
     }
 
-    // Templates [z0, z1) of segment s.  H holds bank row z0 on entry; each
-    // template's successor row (row 0 after the last template, ready for the
+    // Templates [z0, z1) of segment s, the workgroup's templates turn, turn + 1, ..
+    // (see give_way).  H holds bank row z0 on entry; each template's successor row (row 0 after the last template, ready for the
     // next segment) is loaded into H as soon as the first inverse pass has
     // consumed it, so the load overlaps the rest of the transform without a
     // second register buffer.
@@ -331,7 +353,7 @@ struct Fwd {
                                 const float2* __restrict__ bank, int K, int M, int64_t s, int z0,
                                 int z1, float* __restrict__ plane, const typename F::TW& tw,
                                 float2*& la, float2*& lb, int t, float2 (&H)[E],
-                                const float2* __restrict__ bank2 = nullptr,
+                                int& turn, const float2* __restrict__ bank2 = nullptr,
                                 float2* __restrict__ edge = nullptr)
     {
         const int B = L - M;
@@ -346,6 +368,7 @@ struct Fwd {
         // bank, z < c), consumed reversed and conjugated.
         auto one = [&](int z, auto mir_tag) {
             constexpr bool MIR = decltype(mir_tag)::value;
+            give_way(turn++);
             float2 v[E];
             const int znext = z + 1 == K ? 0 : z + 1;
             auto next = [&]() { load_bank_row<SYM>(H, bank, znext, K, t); };
@@ -525,12 +548,13 @@ __global__ __launch_bounds__(Fwd<L>::T, 2) void forward_kernel(
     float2* lb = lds[1];
     float2 H[W::E];
     W::template load_bank_row<SYM>(H, bank, (int)(i % K), K, t);
+    int turn = 0;
     while (i < i1) {
         const int64_t s = i / K;
         const int zs = (int)(i - s * K);
         const int ze = (int)min<int64_t>(K, zs + (i1 - i));
         W::template item<IB, SYM, DUAL, DEAD>(spec, N, bank, K, M, s, zs, ze, plane, tw, la, lb,
-                                               t, H, bank2, edge);
+                                               t, H, turn, bank2, edge);
         i += ze - zs;
     }
 }
@@ -634,6 +658,7 @@ __global__ __launch_bounds__((Fwd<L, E>::T), 2) void batched_kernel(
     float2* lb = lds[1];
     float2 H[W::E];
     W::load_row(H, bank, (int)(i % K), t);
+    int turn = 0;
     while (i < i1) {
         const int64_t tile = i / K;
         const int zs = (int)(i - tile * K);
@@ -643,7 +668,8 @@ __global__ __launch_bounds__((Fwd<L, E>::T), 2) void batched_kernel(
         spec_range(offsets, b, cap, off, Nb);
         W::template item<false, false, false, DEAD>(specs + off, Nb, bank, K, M,
                                                     tile - segpre[b], zs, ze,
-                                                    planes + (int64_t)K * off, tw, la, lb, t, H);
+                                                    planes + (int64_t)K * off, tw, la, lb, t, H,
+                                                    turn);
         i += ze - zs;
     }
 }

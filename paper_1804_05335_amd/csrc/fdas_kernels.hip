@@ -232,9 +232,12 @@ hipError_t launch_prepare_bank(const float2* taps, int K, int M, int L, float2* 
 // of its time.  Every workgroup therefore starts its n-th template at priority 3 -
 // n mod 4: the one ahead gives way until the others have caught up, and they end
 // within 5 % of one another.  Measured: that plane 232 -> 217 us, the two-bin
-// plane of 300007 bins (K = 41, M = 128, L = 1024) 36.0 -> 34.6 us, the plane of
-// 2^20 bins at K = 85, M = 128, L = 512 111 -> 103 us; the plane of 2^21 bins at
-// L = 2048, where the four workgroups differ less, unchanged.
+// plane of 300007 bins (K = 41, M = 128, L = 1024) 37.8 -> 37.1 us; the plane of
+// 2^21 bins at L = 2048, where the four workgroups differ less, unchanged.  Not
+// below L = 1024, whose one-wave workgroups pay more for the branch than they
+// gain (300001 bins, K = 85, M = 64, L = 512: 39.1 -> 41.5 us), nor at L = 8192,
+// where one workgroup fills the CU and the two-bin kernel has no register to
+// spare for the count (709 -> 1020 us).
 __device__ __forceinline__ void give_way(int n)
 {
 #ifdef __HIP_DEVICE_COMPILE__   // the host pass and the CPU emulation have no priorities
@@ -368,7 +371,8 @@ struct Fwd {
         // bank, z < c), consumed reversed and conjugated.
         auto one = [&](int z, auto mir_tag) {
             constexpr bool MIR = decltype(mir_tag)::value;
-            give_way(turn++);
+            if constexpr (L >= 1024 && L <= 4096)
+                give_way(turn++);
             float2 v[E];
             const int znext = z + 1 == K ? 0 : z + 1;
             auto next = [&]() { load_bank_row<SYM>(H, bank, znext, K, t); };

@@ -20,6 +20,8 @@
 // and keeps them in registers for every transform it runs.
 #pragma once
 
+#include <cstdint>
+
 #include <hip/hip_runtime.h>
 
 namespace fdas {
@@ -296,11 +298,6 @@ struct PairWrites {
     static constexpr bool value = L >= 8192;
 };
 
-template <int L>
-struct LdsSize {
-    static constexpr int value = L;
-};
-
 // Load the twiddles for passes NS.. into tw[OFF..] (all but the pass of
 // stride LNS).
 template <int L, int E, int NS, int OFF, int NTW, int LNS, int R, int... Rest>
@@ -455,6 +452,8 @@ struct FFT<L, E, Radices<Rs...>> {
     static constexpr int kLdsTwAlloc = kLdsTw > 0 ? kLdsTw : 1;
     static constexpr int NTW = TwiddleCount<L, E, 1, kLNS, Radices<Rs...>>::value > 0
                                    ? TwiddleCount<L, E, 1, kLNS, Radices<Rs...>>::value : 1;
+    // exchange buffers: kLds values, the second from kLdsSplit on
+    static constexpr int kLds = 2 * L, kLdsSplit = L;
     static_assert((1 * ... * Rs) == L, "radices must multiply to L");
     static_assert(((E % Rs == 0) && ...), "every radix must divide E");
 
@@ -516,17 +515,249 @@ struct FFT<L, E, Radices<Rs...>> {
     }
 };
 
+// ---- eight values per lane: transforms split over waves ------------------------
+//
+// L = 512 W on W = 2, 4 or 8 waves, lane t = 64 w + l holding positions t + T m on
+// both sides as above.  Written with index bits: a position before the first pass
+// is p = [3 register bits][b wave bits][6 lane bits], W = 2^b, and the passes take
+// p's bits from the top, three at a time, turning them into the bits of the output
+// index n from the bottom.  Which bits sit in the wave index between the passes is
+// free, and chosen so that only two exchanges cross waves:
+//   pass 1  registers p[8+b .. 6+b]   waves p[5+b .. 6]    lanes p[5 .. 0]
+//   pass 2  registers p[5+b .. 3+b]   waves p[b-1 .. 0]    lanes p[2+b .. b], n[2..0]
+//   pass 3  registers p[2+b .. b]     waves p[b-1 .. 0]    lanes n[5..0]
+//   pass 4  registers p[b-1 .. 0], n  waves n[5+b .. 6]    lanes n[5..0]
+// Passes 1 to 3 are of radix 8, the last of radix W.  The exchange between passes 2
+// and 3 stays inside each wave, whose LDS accesses execute in order, so it needs
+// no barrier.
+//
+// LDS: every wave writes only its own region, of buffer A in the first exchange
+// and of buffer B in the other two, so two barriers per transform suffice: a
+// region of A is rewritten after the last exchange's barrier, which follows
+// everybody's reads of A; a region of B after the first exchange's barrier, which
+// follows everybody's reads of B.  The places of the index bits inside a region
+// (strides that add up, so that one base register and immediate offsets address a
+// whole exchange) keep the accesses free of bank conflicts: the low four lane bits
+// of a write have strides with distinct sums mod 16, the low five of a read mod 32.
+//   first exchange   n: 4 each, then stride_a: two of p's bits at 1 and 2, the
+//                    rest at 36, 72, 140 (146), 280 (286)
+//   second exchange  n[2..0]: 1, n[5..3]: 8, p: 72
+//   third exchange   lane + 64 n[8..6]
+//
+// Used where a lane keeps several transform-sized arrays, the adjoint from L =
+// 1024 to 4096: the exchanges' addresses take 6 registers instead of ~40, so with
+// both gradients three waves fit a SIMD instead of two, and a transform has two
+// barriers instead of three.  Measured for both gradients: 2^19 bins, K = 85, M =
+// 256, L = 2048 277 -> 219 us, L = 1024 258 -> 220 us, 300000 bins, K = 201, M =
+// 512, L = 4096 503 -> 468 us; the spectrum's alone 160 -> 159, 146 -> 146, 354
+// -> 358 us.  The forward kernels keep 16 values per lane from L = 1024 on: with
+// four waves per SIMD of this transform the plane of 2^21 bins, K = 85, M = 256
+// took 252 us against 243, since its three exchanges move half as much again
+// through LDS.
+struct WaveSplit {};
+
+// Orders a wave's LDS accesses for the compiler (the hardware keeps them in
+// order).
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// One 64-bit LDS read or write.  As relaxed atomics, because the compiler would
+// merge neighbouring plain accesses into pairs (ds_read2_b64, ds_write2_b64),
+// which LDS serves more slowly (measured per CU and clock: reads 234 bytes as
+// singles and 128 as pairs, writes 82 and 77).
+__device__ __forceinline__ float2 lds_read(const float2* p)
+{
+    const uint64_t u = __atomic_load_n(reinterpret_cast<const uint64_t*>(p), __ATOMIC_RELAXED);
+    return make_float2(__uint_as_float((unsigned)u), __uint_as_float((unsigned)(u >> 32)));
+}
+
+__device__ __forceinline__ void lds_write(float2* p, float2 v)
+{
+    const uint64_t u = (uint64_t)__float_as_uint(v.x) | (uint64_t)__float_as_uint(v.y) << 32;
+    __atomic_store_n(reinterpret_cast<uint64_t*>(p), u, __ATOMIC_RELAXED);
+}
+
+// The order in which a pass of radix R first uses its inputs: LDS returns a
+// wave's reads in order.
+template <int R>
+__device__ constexpr int order(int n)
+{
+    constexpr int o8[8] = {0, 4, 2, 6, 1, 5, 3, 7};
+    constexpr int o4[4] = {0, 2, 1, 3};
+    return R == 8 ? o8[n & 7] : (R == 4 ? o4[n & 3] : n);
+}
+
+template <int L, int E, class RL>
+struct FFT;
+
+template <int L>
+struct FFT<L, 8, WaveSplit> {
+    static constexpr int T = L / 8;
+    static constexpr int W = T / 64;
+    static constexpr int b = W == 8 ? 3 : (W == 4 ? 2 : 1);
+    static_assert(L == 512 << b, "1024 to 4096 points");
+    static constexpr int NB = 8 / W;                    // last pass: butterflies per lane
+    static constexpr int kLastTw = W - 1;               // twiddles of one of them
+    static constexpr int NTW = 14 + NB * kLastTw;
+    static constexpr int kRegionA = b == 3 ? 572 : 560, kRegionB = 568;
+    static constexpr int kLdsSplit = W * kRegionA, kLds = W * (kRegionA + kRegionB);
+    static constexpr int kLdsTwAlloc = 1;
+
+    struct TW {
+        float2 r[NTW];
+    };
+
+    // stride of p's bit k in the first exchange (bits 6 .. 5 + b: the region)
+    __device__ static constexpr int stride_a(int k)
+    {
+        constexpr int s[3][6] = {{36, 1, 2, 72, 140, 280},
+                                 {36, 72, 1, 2, 140, 280},
+                                 {36, 72, 146, 1, 2, 286}};
+        return k < 6 ? s[b - 1][k] : kRegionA << (k - 6);
+    }
+    // sum of the strides of p's bits first .. first + n - 1 that are set in x
+    template <int N>
+    __device__ static int place_a(int x, int first)
+    {
+        int a = 0;
+#pragma unroll
+        for (int k = 0; k < N; ++k)
+            a += ((x >> k) & 1) * stride_a(first + k);
+        return a;
+    }
+
+    __device__ static void twiddles(TW& tw, const float2* __restrict__ table, float2*, int t)
+    {
+        const int lane = t & 63;
+#pragma unroll
+        for (int i = 1; i < 8; ++i) {
+            tw.r[i - 1] = table[(lane & 7) * i * (L / 64)];
+            tw.r[6 + i] = table[lane * i * (L / 512)];
+        }
+#pragma unroll
+        for (int u = 0; u < NB; ++u)
+#pragma unroll
+            for (int i = 1; i < W; ++i)
+                tw.r[14 + u * kLastTw + i - 1] = table[(t + T * u) * i];
+    }
+
+    // DFT_R of x_i w^i with the twiddles w, .., w^(R-1)
+    template <int R, bool INV>
+    __device__ static void twiddled(float2 (&x)[R], const float2* tw)
+    {
+        float2 w[R];
+        w[0] = make_float2(1.f, 0.f);
+#pragma unroll
+        for (int i = 1; i < R; ++i)
+            w[i] = tw[i - 1];
+        dft_mul<R, INV, INV ? kMulConj : kMul, true>(x, w);
+    }
+
+    template <bool INV, int MODE, class Hook>
+    __device__ static void passes(const float2 (&in)[8], const float2 (&pre)[8], float2 (&v)[8],
+                                  float2* A, float2* B, const TW& tw, int t, Hook& hook)
+    {
+        const int lane = t & 63, wave = t >> 6;
+        {
+            float2 x[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                x[i] = in[i];
+            dft_mul<8, INV, MODE, false>(x, pre);
+            float2* w = A + wave * kRegionA + place_a<6>(lane, 0);
+#pragma unroll
+            for (int n = 0; n < 8; ++n)
+                lds_write(w + 4 * n, x[n]);
+        }
+        hook();     // `in` and `pre` are no longer read: their registers may be reloaded
+        __syncthreads();
+        {
+            const float2* r = A + 4 * (lane & 7) + place_a<3>(lane >> 3, b) + place_a<b>(wave, 0);
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const int m = order<8>(k);
+                v[m] = lds_read(r + (m & 1) * stride_a(b + 3) + (m >> 1 & 1) * stride_a(b + 4) +
+                                (m >> 2) * stride_a(b + 5));
+            }
+        }
+        twiddled<8, INV>(v, tw.r);
+        float2* own = B + wave * kRegionB;
+        {
+            float2* w = own + (lane & 7) + 72 * (lane >> 3);
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                lds_write(w + 8 * i, v[i]);
+            wave_sync();
+            const float2* r = own + lane;
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+                v[order<8>(k)] = lds_read(r + 72 * order<8>(k));
+        }
+        twiddled<8, INV>(v, tw.r + 7);
+        wave_sync();
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            lds_write(own + lane + 64 * i, v[i]);
+        __syncthreads();
+        const float2* r = B + lane + 64 * wave;
+#pragma unroll
+        for (int u = 0; u < NB; ++u) {
+            float2 x[W];
+#pragma unroll
+            for (int k = 0; k < W; ++k) {
+                const int i = order<W>(k);
+                x[i] = lds_read(r + i * kRegionB + ((64 * u) << b));
+            }
+            twiddled<W, INV>(x, tw.r + 14 + u * kLastTw);
+#pragma unroll
+            for (int i = 0; i < W; ++i)
+                v[u + i * NB] = x[i];
+        }
+    }
+
+    template <bool INV>
+    __device__ static void run(float2 (&v)[8], float2*& a, float2*& bb, const TW& tw, int t)
+    {
+        NoHook none;
+        passes<INV, kNoMul>(v, v, v, a, bb, tw, t, none);
+    }
+    template <bool INV, class Hook>
+    __device__ static void run_hook(float2 (&v)[8], float2*& a, float2*& bb, const TW& tw, int t,
+                                    Hook& hook)
+    {
+        passes<INV, kNoMul>(v, v, v, a, bb, tw, t, hook);
+    }
+    template <bool INV, int MODE>
+    __device__ static void run_mul(const float2 (&in)[8], const float2 (&pre)[8], float2 (&v)[8],
+                                   float2*& a, float2*& bb, const TW& tw, int t)
+    {
+        NoHook none;
+        passes<INV, MODE>(in, pre, v, a, bb, tw, t, none);
+    }
+    template <bool INV, int MODE, class Hook>
+    __device__ static void run_mul_hook(const float2 (&in)[8], const float2 (&pre)[8],
+                                        float2 (&v)[8], float2*& a, float2*& bb, const TW& tw,
+                                        int t, Hook& hook)
+    {
+        passes<INV, MODE>(in, pre, v, a, bb, tw, t, hook);
+    }
+};
+
 // Radix sequence for a length-L transform with E values per lane (every
 // radix divides E, their product is L).
 template <int L, int E>
 struct Plan;
 template <> struct Plan<256, 4>   { using R = Radices<4, 4, 4, 4>; };
 template <> struct Plan<512, 8>   { using R = Radices<8, 8, 8>; };
-template <> struct Plan<1024, 8>  { using R = Radices<8, 8, 8, 2>; };
+template <> struct Plan<1024, 8>  { using R = WaveSplit; };
 template <> struct Plan<1024, 16> { using R = Radices<16, 16, 4>; };
-template <> struct Plan<2048, 8>  { using R = Radices<8, 8, 8, 4>; };
+template <> struct Plan<2048, 8>  { using R = WaveSplit; };
 template <> struct Plan<2048, 16> { using R = Radices<16, 16, 8>; };
-template <> struct Plan<4096, 8>  { using R = Radices<8, 8, 8, 8>; };
+template <> struct Plan<4096, 8>  { using R = WaveSplit; };
 template <> struct Plan<4096, 16> { using R = Radices<16, 16, 16>; };
 template <> struct Plan<8192, 8>  { using R = Radices<8, 8, 8, 8, 2>; };
 template <> struct Plan<8192, 16> { using R = Radices<16, 16, 16, 2>; };

@@ -536,7 +536,7 @@ __global__ __launch_bounds__(Fwd<L>::T, 2) void forward_kernel(
     int64_t nseg, float* __restrict__ plane, const float2* __restrict__ bank2)
 {
     using W = Fwd<L>;
-    __shared__ __align__(16) float2 lds[2][LdsSize<L>::value];
+    __shared__ __align__(16) float2 lds[W::F::kLds];
     __shared__ float2 twl[W::F::kLdsTwAlloc];
     __shared__ __align__(16) float2 edge[IB ? W::kEdgeAlloc : 1];   // interbinning
     int64_t i, i1;
@@ -548,8 +548,8 @@ __global__ __launch_bounds__(Fwd<L>::T, 2) void forward_kernel(
     const int rows = SYM ? (K + 1) / 2 : K;      // bank rows before the twiddle row
     W::F::twiddles(tw, bank + (int64_t)rows * L, twl, t);
     __syncthreads();
-    float2* la = lds[0];
-    float2* lb = lds[1];
+    float2* la = lds;
+    float2* lb = lds + W::F::kLdsSplit;
     float2 H[W::E];
     W::template load_bank_row<SYM>(H, bank, (int)(i % K), K, t);
     int turn = 0;
@@ -648,7 +648,7 @@ __global__ __launch_bounds__((Fwd<L, E>::T), 2) void batched_kernel(
     int K, int M, float* __restrict__ planes)
 {
     using W = Fwd<L, E>;
-    __shared__ __align__(16) float2 lds[2][LdsSize<L>::value];
+    __shared__ __align__(16) float2 lds[W::F::kLds];
     __shared__ float2 twl[W::F::kLdsTwAlloc];
     int64_t i, i1;
     item_range(segpre[nspec] * K, i, i1);
@@ -658,8 +658,8 @@ __global__ __launch_bounds__((Fwd<L, E>::T), 2) void batched_kernel(
     typename W::F::TW tw;
     W::F::twiddles(tw, bank + (int64_t)K * L, twl, t);
     __syncthreads();
-    float2* la = lds[0];
-    float2* lb = lds[1];
+    float2* la = lds;
+    float2* lb = lds + W::F::kLdsSplit;
     float2 H[W::E];
     W::load_row(H, bank, (int)(i % K), t);
     int turn = 0;
@@ -920,14 +920,14 @@ __global__ __launch_bounds__(Bwd<L>::T, WANT_T ? BwdGeometry<L>::kMinWaves
     float2* __restrict__ partA, float2* __restrict__ partT)
 {
     using Bk = Bwd<L>;
-    __shared__ __align__(16) float2 lds[2][LdsSize<L>::value];
+    __shared__ __align__(16) float2 lds[Bk::F::kLds];
     __shared__ float2 twl[Bk::F::kLdsTwAlloc];
     const int t = threadIdx.x;
     typename Bk::F::TW tw;
     Bk::F::twiddles(tw, bank + (int64_t)K * L, twl, t);
     __syncthreads();
-    float2* la = lds[0];
-    float2* lb = lds[1];
+    float2* la = lds;
+    float2* lb = lds + Bk::F::kLdsSplit;
     const int64_t s = blockIdx.x;
     const int c = blockIdx.y;
     const int z0 = c * zchunk;
@@ -1062,7 +1062,7 @@ backward_batched_kernel(const float2* __restrict__ specs, const int64_t* __restr
                         float2* __restrict__ partT)
 {
     using Bk = Bwd<L>;
-    __shared__ __align__(16) float2 lds[2][LdsSize<L>::value];
+    __shared__ __align__(16) float2 lds[Bk::F::kLds];
     __shared__ float2 twl[Bk::F::kLdsTwAlloc];
     const int64_t nw = min(winpre[nspec], maxwin);
     const int c = blockIdx.y;
@@ -1076,8 +1076,8 @@ backward_batched_kernel(const float2* __restrict__ specs, const int64_t* __restr
     typename Bk::F::TW tw;
     Bk::F::twiddles(tw, bank + (int64_t)K * L, twl, t);
     __syncthreads();
-    float2* la = lds[0];
-    float2* lb = lds[1];
+    float2* la = lds;
+    float2* lb = lds + Bk::F::kLdsSplit;
     float2 H[Bk::E];
     Bk::W::load_row(H, bank, z0, t);
     if constexpr (NW == 1) {

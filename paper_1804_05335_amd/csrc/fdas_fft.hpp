@@ -244,6 +244,30 @@ __device__ __forceinline__ void dft_mul(float2 (&x)[R], const float2 (&w)[R])
 template <int... Rs>
 struct Radices {};
 
+// The same with a last pass of radix 2 that takes its values from registers: its
+// butterflies pair positions L/2 apart, and with the lanes l and l + 32 of a wave
+// at places T/2 apart (PassFFT::place) they are the two lanes' outputs of the pass
+// before, exchanged by the half-wave swaps of gfx950 instead of through LDS.  The
+// arithmetic is that of Radices.
+template <int... Rs>
+struct SwapLast {};
+
+#ifdef __HIP_DEVICE_COMPILE__
+constexpr bool kHaveSwap = true;
+// Swaps a of the upper 32 lanes with b of the lower 32.
+__device__ __forceinline__ void swap_halves(float& a, float& b)
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false,
+                                                    false);
+    a = __uint_as_float(r[0]);
+    b = __uint_as_float(r[1]);
+}
+#else
+// the host pass and the CPU emulation exchange through LDS like the other passes
+constexpr bool kHaveSwap = false;
+__device__ inline void swap_halves(float&, float&) {}
+#endif
+
 // Number of register twiddles a lane keeps for the passes from NS on (the
 // pass whose stride is LNS takes its twiddles from an LDS table instead).
 template <int L, int E, int NS, int LNS, class RL>
@@ -331,8 +355,8 @@ struct NoHook {
     __device__ void operator()() const {}
 };
 
-template <int L, int E, bool INV, int MODE0, int NS, int OFF, int NTW, int LNS, class Hook, int R,
-          int... Rest>
+template <int L, int E, bool SWAP, bool INV, int MODE0, int NS, int OFF, int NTW, int LNS,
+          class Hook, int R, int... Rest>
 __device__ __forceinline__ void run_passes(const float2 (&in)[E], const float2 (&pre)[E],
                                            float2 (&v)[E], float2*& lds_a, float2*& lds_b,
                                            const float2 (&tw)[NTW],
@@ -342,6 +366,7 @@ __device__ __forceinline__ void run_passes(const float2 (&in)[E], const float2 (
     constexpr bool LAST = sizeof...(Rest) == 0;
     constexpr bool REG = NS > 1 && NS != LNS;
     constexpr bool PAIR = PairWrites<L>::value;
+    constexpr bool SWAP_NEXT = SWAP && kHaveSwap && sizeof...(Rest) == 1;
 #pragma unroll
     for (int u = 0; u < NB; ++u) {
         float2 x[R];
@@ -379,6 +404,19 @@ __device__ __forceinline__ void run_passes(const float2 (&in)[E], const float2 (
 #pragma unroll
             for (int i = 0; i < R; ++i)
                 v[u + i * NB] = x[i];
+        } else if constexpr (SWAP_NEXT) {
+            // the last pass pairs positions L/2 apart: this lane's outputs and
+            // those of the lane 32 away (see SwapLast); of each two neighbours the
+            // lower half keeps the even ones, the upper half the odd ones
+            static_assert(R == E && 2 * NS * R == L, "one butterfly, then radix 2");
+#pragma unroll
+            for (int i = 0; i < R / 2; ++i) {
+                float2 a = x[2 * i], b = x[2 * i + 1];
+                swap_halves(a.x, b.x);
+                swap_halves(a.y, b.y);
+                v[i] = a;
+                v[i + R / 2] = b;
+            }
         } else if constexpr (NS == 1 && PAIR) {
             // butterfly j's outputs are the contiguous values j R .. j R + R - 1:
             // adjacent pairs go out as single 128-bit stores
@@ -399,15 +437,17 @@ __device__ __forceinline__ void run_passes(const float2 (&in)[E], const float2 (
     if constexpr (NS == 1)
         hook();     // `in` and `pre` are no longer read: their registers may be reloaded
     if constexpr (!LAST) {
-        __syncthreads();
+        if constexpr (!SWAP_NEXT) {
+            __syncthreads();
 #pragma unroll
-        for (int m = 0; m < E; ++m)
-            v[m] = lds_a[lds_pad<PAIR>(t + m * T)];
-        float2* tmp = lds_a;
-        lds_a = lds_b;
-        lds_b = tmp;
+            for (int m = 0; m < E; ++m)
+                v[m] = lds_a[lds_pad<PAIR>(t + m * T)];
+            float2* tmp = lds_a;
+            lds_a = lds_b;
+            lds_b = tmp;
+        }
         NoHook none;
-        run_passes<L, E, INV, kNoMul, NS * R, OFF + (REG ? NB * (R - 1) : 0), NTW, LNS, NoHook,
+        run_passes<L, E, SWAP, INV, kNoMul, NS * R, OFF + (REG ? NB * (R - 1) : 0), NTW, LNS, NoHook,
                    Rest...>(v, pre, v, lds_a, lds_b, tw, twl, t, none);
     }
 }
@@ -436,9 +476,15 @@ struct LastRadix<R, R2, Rest...> {
     static constexpr int value = LastRadix<R2, Rest...>::value;
 };
 
-template <int L, int E, int... Rs>
-struct FFT<L, E, Radices<Rs...>> {
+template <int L, int E, bool SWAP, int... Rs>
+struct PassFFT {
     static constexpr int T = L / E;
+    // The place t of lane `thread`: the lane holds positions t + T m.  With SWAP the
+    // lanes l and l + 32 of a wave take places T/2 apart.
+    __device__ static int place(int thread)
+    {
+        return SWAP ? 32 * (thread >> 6) + (thread & 31) + (thread & 32) * (T / 64) : thread;
+    }
     // One pass may take its twiddles from a table in LDS instead of
     // registers: at L = 8192 the last one (radix 2, stride L/2: one twiddle
     // per butterfly, a 32 KB table), which frees the registers the longest
@@ -484,16 +530,17 @@ struct FFT<L, E, Radices<Rs...>> {
     __device__ static void run(float2 (&v)[E], float2*& lds_a, float2*& lds_b, const TW& tw, int t)
     {
         NoHook none;
-        run_passes<L, E, INV, kNoMul, 1, 0, NTW, kLNS, NoHook, Rs...>(v, v, v, lds_a, lds_b, tw.r,
-                                                                      tw.lds, t, none);
+        run_passes<L, E, SWAP, INV, kNoMul, 1, 0, NTW, kLNS, NoHook, Rs...>(v, v, v, lds_a, lds_b,
+                                                                            tw.r, tw.lds, t,
+                                                                            none);
     }
     // as run; hook() runs once the first pass has read v
     template <bool INV, class Hook>
     __device__ static void run_hook(float2 (&v)[E], float2*& lds_a, float2*& lds_b, const TW& tw,
                                     int t, Hook& hook)
     {
-        run_passes<L, E, INV, kNoMul, 1, 0, NTW, kLNS, Hook, Rs...>(v, v, v, lds_a, lds_b, tw.r,
-                                                                    tw.lds, t, hook);
+        run_passes<L, E, SWAP, INV, kNoMul, 1, 0, NTW, kLNS, Hook, Rs...>(v, v, v, lds_a, lds_b,
+                                                                          tw.r, tw.lds, t, hook);
     }
     // v = transform of in[m] * pre[m] (MODE kMul) or in[m] * conj(pre[m]) (kMulConj)
     template <bool INV, int MODE>
@@ -501,8 +548,8 @@ struct FFT<L, E, Radices<Rs...>> {
                                    float2*& lds_a, float2*& lds_b, const TW& tw, int t)
     {
         NoHook none;
-        run_passes<L, E, INV, MODE, 1, 0, NTW, kLNS, NoHook, Rs...>(in, pre, v, lds_a, lds_b,
-                                                                    tw.r, tw.lds, t, none);
+        run_passes<L, E, SWAP, INV, MODE, 1, 0, NTW, kLNS, NoHook, Rs...>(in, pre, v, lds_a, lds_b,
+                                                                          tw.r, tw.lds, t, none);
     }
     // as run_mul; hook() runs once the first pass has consumed `in` and `pre`
     template <bool INV, int MODE, class Hook>
@@ -510,8 +557,8 @@ struct FFT<L, E, Radices<Rs...>> {
                                         float2 (&v)[E], float2*& lds_a, float2*& lds_b,
                                         const TW& tw, int t, Hook& hook)
     {
-        run_passes<L, E, INV, MODE, 1, 0, NTW, kLNS, Hook, Rs...>(in, pre, v, lds_a, lds_b, tw.r,
-                                                                  tw.lds, t, hook);
+        run_passes<L, E, SWAP, INV, MODE, 1, 0, NTW, kLNS, Hook, Rs...>(in, pre, v, lds_a, lds_b,
+                                                                        tw.r, tw.lds, t, hook);
     }
 };
 
@@ -606,6 +653,8 @@ struct FFT<L, 8, WaveSplit> {
     static constexpr int kRegionA = b == 3 ? 572 : 560, kRegionB = 568;
     static constexpr int kLdsSplit = W * kRegionA, kLds = W * (kRegionA + kRegionB);
     static constexpr int kLdsTwAlloc = 1;
+
+    __device__ static int place(int thread) { return thread; }
 
     struct TW {
         float2 r[NTW];
@@ -747,6 +796,11 @@ struct FFT<L, 8, WaveSplit> {
     }
 };
 
+template <int L, int E, int... Rs>
+struct FFT<L, E, Radices<Rs...>> : PassFFT<L, E, false, Rs...> {};
+template <int L, int E, int... Rs>
+struct FFT<L, E, SwapLast<Rs...>> : PassFFT<L, E, true, Rs...> {};
+
 // Radix sequence for a length-L transform with E values per lane (every
 // radix divides E, their product is L).
 template <int L, int E>
@@ -761,6 +815,19 @@ template <> struct Plan<4096, 8>  { using R = WaveSplit; };
 template <> struct Plan<4096, 16> { using R = Radices<16, 16, 16>; };
 template <> struct Plan<8192, 8>  { using R = Radices<8, 8, 8, 8, 2>; };
 template <> struct Plan<8192, 16> { using R = Radices<16, 16, 16, 2>; };
+
+// The plan the kernels use: at L = 8192 the last pass takes its values by the
+// half-wave swaps, which leaves two exchanges per transform (and so the exchange
+// buffers in the same parity for every transform, their addresses constant).  The
+// interbinned kernel keeps Plan: its neighbouring outputs sit in neighbouring lanes.
+// Measured, plan with three exchanges -> this one: plane of 2^20 bins, K = 201, M =
+// 512: 453 -> 411 us, its adjoint with both gradients 4299 -> 3603 us, spectrum only
+// 4150 -> 2466 us (fewer spilled registers); both planes of 300001 bins, M = 512:
+// 226 -> 128 us (no spills where there were).  The VALU takes 694 instructions per
+// template instead of 742, the swaps among them, the LDS pipe 60 instead of 93.
+template <int L, int E>
+struct SwapPlan { using R = typename Plan<L, E>::R; };
+template <> struct SwapPlan<8192, 16> { using R = SwapLast<16, 16, 16, 2>; };
 
 // Values per lane of the forward kernels: 16 from L = 1024 on (two LDS
 // exchanges per transform, 256 VGPRs, 2 waves per SIMD), fewer below so a

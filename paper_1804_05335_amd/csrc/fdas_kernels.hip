@@ -267,10 +267,10 @@ constexpr float kQuarterPi2 = 0.61685027506808491368f;   // (pi/4)^2, interbinni
 // Nothing but the valid plane values reaches HBM (Sec. 4.2 first paragraph).
 // The LDS ping-pong buffers la/lb keep alternating across calls, so a
 // workgroup's consecutive work needs no extra barrier.
-template <int L, int EV = Geometry<L>::E>
+template <int L, int EV = Geometry<L>::E, bool IB_PLAN = false>
 struct Fwd {
     static constexpr int E = EV;
-    using F = FFT<L, E, typename Plan<L, E>::R>;
+    using F = FFT<L, E, typename std::conditional_t<IB_PLAN, Plan<L, E>, SwapPlan<L, E>>::R>;
     static constexpr int T = F::T;
     static constexpr int NTW = F::NTW;
     // interbinned epilogue: waves per workgroup, and the `edge` slots
@@ -535,7 +535,7 @@ __global__ __launch_bounds__(Fwd<L>::T, 2) void forward_kernel(
     const float2* __restrict__ spec, int64_t N, const float2* __restrict__ bank, int K, int M,
     int64_t nseg, float* __restrict__ plane, const float2* __restrict__ bank2)
 {
-    using W = Fwd<L>;
+    using W = Fwd<L, Geometry<L>::E, IB>;
     __shared__ __align__(16) float2 lds[W::F::kLds];
     __shared__ float2 twl[W::F::kLdsTwAlloc];
     __shared__ __align__(16) float2 edge[IB ? W::kEdgeAlloc : 1];   // interbinning
@@ -543,7 +543,7 @@ __global__ __launch_bounds__(Fwd<L>::T, 2) void forward_kernel(
     item_range(nseg * K, i, i1);
     if (i >= i1)
         return;     // uniform across the workgroup, before any barrier
-    const int t = threadIdx.x;
+    const int t = W::F::place(threadIdx.x);
     typename W::F::TW tw;
     const int rows = SYM ? (K + 1) / 2 : K;      // bank rows before the twiddle row
     W::F::twiddles(tw, bank + (int64_t)rows * L, twl, t);
@@ -654,7 +654,7 @@ __global__ __launch_bounds__((Fwd<L, E>::T), 2) void batched_kernel(
     item_range(segpre[nspec] * K, i, i1);
     if (i >= i1)
         return;
-    const int t = threadIdx.x;
+    const int t = W::F::place(threadIdx.x);
     typename W::F::TW tw;
     W::F::twiddles(tw, bank + (int64_t)K * L, twl, t);
     __syncthreads();
@@ -922,7 +922,7 @@ __global__ __launch_bounds__(Bwd<L>::T, WANT_T ? BwdGeometry<L>::kMinWaves
     using Bk = Bwd<L>;
     __shared__ __align__(16) float2 lds[Bk::F::kLds];
     __shared__ float2 twl[Bk::F::kLdsTwAlloc];
-    const int t = threadIdx.x;
+    const int t = Bk::F::place(threadIdx.x);
     typename Bk::F::TW tw;
     Bk::F::twiddles(tw, bank + (int64_t)K * L, twl, t);
     __syncthreads();
@@ -1072,7 +1072,7 @@ backward_batched_kernel(const float2* __restrict__ specs, const int64_t* __restr
     const int64_t g = (int64_t)blockIdx.z * gridDim.x + blockIdx.x;   // window, or group
     if (g * NW >= nw)
         return;     // uniform across the workgroup, before any barrier
-    const int t = threadIdx.x;
+    const int t = Bk::F::place(threadIdx.x);
     typename Bk::F::TW tw;
     Bk::F::twiddles(tw, bank + (int64_t)K * L, twl, t);
     __syncthreads();

@@ -49,6 +49,17 @@ __device__ __forceinline__ float2 root(int64_t e, int log2D)
     return make_float2((float)c, (float)s);
 }
 
+// The tile of a workgroup.  Consecutive workgroups go round the 8 XCDs; with
+// `group` > 1 (it divides gridDim.x / 8) each XCD takes `group` consecutive tiles
+// instead, whose rows lie side by side in memory, so the lines that two tiles share
+// (a mirror's rows start one value past a line) meet in one L2, and its misses reach
+// longer runs of a row.
+__device__ __forceinline__ int tile_of_block(int group)
+{
+    const int b = (int)blockIdx.x;
+    return group == 1 ? b : b / (8 * group) * (8 * group) + (b % 8) * group + b / 8 % group;
+}
+
 template <int RB>
 __device__ __forceinline__ void dft_small(float2 (&x)[RB])
 {
@@ -122,7 +133,7 @@ __device__ __forceinline__ void tile_stages(float2 (&x)[16], int g, int i2, floa
 template <int RB, bool FIRST>
 __global__ __launch_bounds__(kR2cThreads) void r2c_pass_kernel(
     const float2* __restrict__ in, float2* __restrict__ out, int log2N, int log2NS,
-    int64_t in_stride, int64_t out_stride)
+    int64_t in_stride, int64_t out_stride, int group)
 {
     // series blockIdx.y of a batch (stride 0 and one series otherwise)
     in += (int64_t)blockIdx.y * in_stride;
@@ -135,7 +146,7 @@ __global__ __launch_bounds__(kR2cThreads) void r2c_pass_kernel(
     const int t = threadIdx.x;
     const int NS = 1 << log2NS;
     const int64_t stride = (int64_t)1 << (log2N - S::logR);   // N / R
-    const int64_t j0 = (int64_t)blockIdx.x * G;
+    const int64_t j0 = (int64_t)tile_of_block(group) * G;
 
     const int g = t % G, i2 = t / G;
     const int64_t j = j0 + g;
@@ -199,7 +210,7 @@ __global__ __launch_bounds__(kR2cThreads) void r2c_pass_kernel(
 template <int RB>
 __global__ __launch_bounds__(2 * kR2cThreads, 4) void r2c_last_split_kernel(
     const float2* __restrict__ in, float2* __restrict__ A, int log2N, int log2n, float scale,
-    int64_t in_stride, int64_t out_stride)
+    int64_t in_stride, int64_t out_stride, int group)
 {
     in += (int64_t)blockIdx.y * in_stride;
     A += (int64_t)blockIdx.y * out_stride;
@@ -216,7 +227,7 @@ __global__ __launch_bounds__(2 * kR2cThreads, 4) void r2c_last_split_kernel(
     const int t = threadIdx.x, h = t / kR2cThreads, tt = t % kR2cThreads;
     const int log2NS = log2N - S::logR;
     const int NS = 1 << log2NS;
-    const int w = blockIdx.x;
+    const int w = tile_of_block(group);
     const int g = tt % G, i2 = tt / G;
     auto butterfly = [&](int hh, int gg) {
         return hh == 0 ? w * G + gg : (w == 0 && gg == 0 ? NS / 2 : NS - w * G - gg);
@@ -308,17 +319,31 @@ __global__ void r2c_split_kernel(const float2* __restrict__ Z, int64_t N, int lo
         A[km] = am;
 }
 
+// Consecutive tiles per XCD (see tile_of_block): 16 from 2^23 complex values in all,
+// where the passes no longer run from the last-level cache alone.  Measured, 1 ->
+// 16: one series of 2^24 samples 69.2 -> 67.5 us, two 153 -> 136, four of 2^23 150 ->
+// 135, one of 2^25 152 -> 135, of 2^26 422 -> 421; below it groups gain nothing (one
+// series of 2^22 27.0 -> 27.9, of 2^20 18.8 -> 19.5 us).  A whole eighth of the grid
+// per XCD times alike up to 2^24 and worse above (2^26: 447 us), 2 to 8 tiles gain
+// less.
+constexpr int kXcdGroup = 16;
+int xcd_group(unsigned blocks, int64_t N, unsigned nser)
+{
+    return N * nser >= (int64_t)1 << 23 && blocks % (8 * kXcdGroup) == 0 ? kXcdGroup : 1;
+}
+
 template <int RB>
 hipError_t pass_L(const float2* in, float2* out, int log2N, int log2NS, bool first,
                   int64_t sin, int64_t sout, unsigned nser, hipStream_t s)
 {
     const dim3 blocks((unsigned)(((int64_t)1 << log2N) / kR2cTile), nser);
+    const int group = xcd_group(blocks.x, (int64_t)1 << log2N, nser);
     if (first)
         hipLaunchKernelGGL((r2c_pass_kernel<RB, true>), blocks, dim3(kR2cThreads), 0, s, in, out,
-                           log2N, log2NS, sin, sout);
+                           log2N, log2NS, sin, sout, group);
     else
         hipLaunchKernelGGL((r2c_pass_kernel<RB, false>), blocks, dim3(kR2cThreads), 0, s, in, out,
-                           log2N, log2NS, sin, sout);
+                           log2N, log2NS, sin, sout, group);
     return hipGetLastError();
 }
 
@@ -328,8 +353,9 @@ hipError_t last_L(const float2* in, float2* A, int log2N, int log2n, float scale
 {
     // NS / (2G) workgroups of 512 lanes per series
     const dim3 blocks((unsigned)(((int64_t)1 << log2N) / (2 * kR2cTile)), nser);
+    const int group = xcd_group(blocks.x, (int64_t)1 << log2N, nser);
     hipLaunchKernelGGL((r2c_last_split_kernel<RB>), blocks, dim3(2 * kR2cThreads), 0, s, in, A,
-                       log2N, log2n, scale, sin, sout);
+                       log2N, log2n, scale, sin, sout, group);
     return hipGetLastError();
 }
 

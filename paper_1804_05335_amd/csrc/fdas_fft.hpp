@@ -244,11 +244,14 @@ __device__ __forceinline__ void dft_mul(float2 (&x)[R], const float2 (&w)[R])
 template <int... Rs>
 struct Radices {};
 
-// The same with a last pass of radix 2 that takes its values from registers: its
-// butterflies pair positions L/2 apart, and with the lanes l and l + 32 of a wave
-// at places T/2 apart (PassFFT::place) they are the two lanes' outputs of the pass
-// before, exchanged by the half-wave swaps of gfx950 instead of through LDS.  The
-// arithmetic is that of Radices.
+// The same with a last pass of radix 2, or of radix 4 in a one-wave workgroup, that
+// takes its values from registers.  Radix 2: its butterflies pair positions L/2
+// apart, and with the lanes l and l + 32 of a wave at places T/2 apart
+// (PassFFT::place) they are the two lanes' outputs of the pass before, exchanged by
+// the half-wave swaps of gfx950 instead of through LDS.  Radix 4: positions L/4 apart
+// are the outputs i of the four rows of 16 lanes, and row b takes i = b mod 4, a 4 x 4
+// exchange of rows and registers by row and half-wave swaps.  The arithmetic is that
+// of Radices.
 template <int... Rs>
 struct SwapLast {};
 
@@ -262,10 +265,19 @@ __device__ __forceinline__ void swap_halves(float& a, float& b)
     a = __uint_as_float(r[0]);
     b = __uint_as_float(r[1]);
 }
+// Swaps a of the odd rows of 16 lanes with b of the even row before each.
+__device__ __forceinline__ void swap_rows(float& a, float& b)
+{
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false,
+                                                    false);
+    a = __uint_as_float(r[0]);
+    b = __uint_as_float(r[1]);
+}
 #else
 // the host pass and the CPU emulation exchange through LDS like the other passes
 constexpr bool kHaveSwap = false;
 __device__ inline void swap_halves(float&, float&) {}
+__device__ inline void swap_rows(float&, float&) {}
 #endif
 
 // Number of register twiddles a lane keeps for the passes from NS on (the
@@ -405,18 +417,29 @@ __device__ __forceinline__ void run_passes(const float2 (&in)[E], const float2 (
             for (int i = 0; i < R; ++i)
                 v[u + i * NB] = x[i];
         } else if constexpr (SWAP_NEXT) {
-            // the last pass pairs positions L/2 apart: this lane's outputs and
-            // those of the lane 32 away (see SwapLast); of each two neighbours the
-            // lower half keeps the even ones, the upper half the odd ones
-            static_assert(R == E && 2 * NS * R == L, "one butterfly, then radix 2");
+            // the last pass's butterflies lie across 2 or 4 lanes (see SwapLast):
+            // of each RN neighbouring outputs every lane keeps one, of all the lanes
+            static_assert(R == E && (2 * NS * R == L || (4 * NS * R == L && T == 64)),
+                          "one butterfly, then radix 2, or radix 4 in one wave");
+            constexpr int RN = L / (NS * R);
+            if constexpr (RN == 4) {
 #pragma unroll
-            for (int i = 0; i < R / 2; ++i) {
-                float2 a = x[2 * i], b = x[2 * i + 1];
-                swap_halves(a.x, b.x);
-                swap_halves(a.y, b.y);
-                v[i] = a;
-                v[i + R / 2] = b;
+                for (int i = 0; i < R; i += 2) {
+                    swap_rows(x[i].x, x[i + 1].x);
+                    swap_rows(x[i].y, x[i + 1].y);
+                }
             }
+            constexpr int D = RN / 2;
+#pragma unroll
+            for (int i = 0; i < R; ++i) {
+                if ((i & D) == 0) {
+                    swap_halves(x[i].x, x[i + D].x);
+                    swap_halves(x[i].y, x[i + D].y);
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < R; ++i)
+                v[i / RN + i % RN * (R / RN)] = x[i];
         } else if constexpr (NS == 1 && PAIR) {
             // butterfly j's outputs are the contiguous values j R .. j R + R - 1:
             // adjacent pairs go out as single 128-bit stores
@@ -442,9 +465,11 @@ __device__ __forceinline__ void run_passes(const float2 (&in)[E], const float2 (
 #pragma unroll
             for (int m = 0; m < E; ++m)
                 v[m] = lds_a[lds_pad<PAIR>(t + m * T)];
-            float2* tmp = lds_a;
-            lds_a = lds_b;
-            lds_b = tmp;
+            if constexpr (!(SWAP && kHaveSwap && T == 64)) {   // one buffer then, see kOneBuffer
+                float2* tmp = lds_a;
+                lds_a = lds_b;
+                lds_b = tmp;
+            }
         }
         NoHook none;
         run_passes<L, E, SWAP, INV, kNoMul, NS * R, OFF + (REG ? NB * (R - 1) : 0), NTW, LNS, NoHook,
@@ -479,11 +504,11 @@ struct LastRadix<R, R2, Rest...> {
 template <int L, int E, bool SWAP, int... Rs>
 struct PassFFT {
     static constexpr int T = L / E;
-    // The place t of lane `thread`: the lane holds positions t + T m.  With SWAP the
-    // lanes l and l + 32 of a wave take places T/2 apart.
+    // The place t of lane `thread`: the lane holds positions t + T m.  For the swaps
+    // before a radix 2 the lanes l and l + 32 of a wave take places T/2 apart.
     __device__ static int place(int thread)
     {
-        return SWAP ? 32 * (thread >> 6) + (thread & 31) + (thread & 32) * (T / 64) : thread;
+        return SWAP && T > 64 ? 32 * (thread >> 6) + (thread & 31) + (thread & 32) * (T / 64) : thread;
     }
     // One pass may take its twiddles from a table in LDS instead of
     // registers: at L = 8192 the last one (radix 2, stride L/2: one twiddle
@@ -499,7 +524,10 @@ struct PassFFT {
     static constexpr int NTW = TwiddleCount<L, E, 1, kLNS, Radices<Rs...>>::value > 0
                                    ? TwiddleCount<L, E, 1, kLNS, Radices<Rs...>>::value : 1;
     // exchange buffers: kLds values, the second from kLdsSplit on
-    static constexpr int kLds = 2 * L, kLdsSplit = L;
+    // (one buffer where one wave makes one exchange per transform: its accesses
+    // execute in order)
+    static constexpr bool kOneBuffer = SWAP && kHaveSwap && T == 64;
+    static constexpr int kLds = kOneBuffer ? L : 2 * L, kLdsSplit = kOneBuffer ? 0 : L;
     static_assert((1 * ... * Rs) == L, "radices must multiply to L");
     static_assert(((E % Rs == 0) && ...), "every radix must divide E");
 
@@ -816,8 +844,8 @@ template <> struct Plan<4096, 16> { using R = Radices<16, 16, 16>; };
 template <> struct Plan<8192, 8>  { using R = Radices<8, 8, 8, 8, 2>; };
 template <> struct Plan<8192, 16> { using R = Radices<16, 16, 16, 2>; };
 
-// The plan the kernels use: at L = 8192 the last pass takes its values by the
-// half-wave swaps, which leaves two exchanges per transform (and so the exchange
+// The plan the kernels use: at L = 1024 and 8192 the last pass takes its values by
+// the lane swaps.  At L = 8192 that leaves two exchanges per transform (and so the exchange
 // buffers in the same parity for every transform, their addresses constant).  The
 // interbinned kernel keeps Plan: its neighbouring outputs sit in neighbouring lanes.
 // Measured, plan with three exchanges -> this one: plane of 2^20 bins, K = 201, M =
@@ -825,9 +853,15 @@ template <> struct Plan<8192, 16> { using R = Radices<16, 16, 16, 2>; };
 // 4150 -> 2466 us (fewer spilled registers); both planes of 300001 bins, M = 512:
 // 226 -> 128 us (no spills where there were).  The VALU takes 694 instructions per
 // template instead of 742, the swaps among them, the LDS pipe 60 instead of 93.
+// At L = 1024, one wave with its lanes in natural order, one exchange and one buffer
+// are left: both planes of 300007 bins, K = 41, M = 128: 36.7 -> 35.9 us, plane of
+// 300001 bins, K = 85, M = 256: 44.9 -> 43.9 us (a swap takes the VALU as long as
+// four FMAs, so only the LDS pipe's share that nothing hid is gained).  Not at L =
+// 256 (4, 4, 4, 4): K = 85, M = 64 46 -> 50 us, M = 128 58 -> 52 us.
 template <int L, int E>
 struct SwapPlan { using R = typename Plan<L, E>::R; };
 template <> struct SwapPlan<8192, 16> { using R = SwapLast<16, 16, 16, 2>; };
+template <> struct SwapPlan<1024, 16> { using R = SwapLast<16, 16, 4>; };
 
 // Values per lane of the forward kernels: 16 from L = 1024 on (two LDS
 // exchanges per transform, 256 VGPRs, 2 waves per SIMD), fewer below so a

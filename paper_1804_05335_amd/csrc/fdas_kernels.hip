@@ -270,7 +270,7 @@ constexpr float kQuarterPi2 = 0.61685027506808491368f;   // (pi/4)^2, interbinni
 template <int L, int EV = Geometry<L>::E, bool IB_PLAN = false>
 struct Fwd {
     static constexpr int E = EV;
-    using F = FFT<L, E, typename std::conditional_t<IB_PLAN, Plan<L, E>, SwapPlan<L, E>>::R>;
+    using F = FFT<L, E, typename std::conditional_t<IB_PLAN && L == 8192, Plan<L, E>, SwapPlan<L, E>>::R>;
     static constexpr int T = F::T;
     static constexpr int NTW = F::NTW;
     // interbinned epilogue: waves per workgroup, and the `edge` slots

@@ -863,8 +863,8 @@ struct SwapPlan { using R = typename Plan<L, E>::R; };
 template <> struct SwapPlan<8192, 16> { using R = SwapLast<16, 16, 16, 2>; };
 template <> struct SwapPlan<1024, 16> { using R = SwapLast<16, 16, 4>; };
 
-// Values per lane of the forward kernels: 16 from L = 1024 on (two LDS
-// exchanges per transform, 256 VGPRs, 2 waves per SIMD), fewer below so a
+// Values per lane of the forward kernels: 16 from L = 1024 on (two LDS exchanges
+// per transform, one at L = 1024; 2 waves per SIMD), fewer below so a
 // transform still spans at least one full wave.
 #ifndef FDAS_FWD_E
 #define FDAS_FWD_E 16

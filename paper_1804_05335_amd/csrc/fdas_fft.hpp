@@ -280,6 +280,15 @@ __device__ inline void swap_halves(float&, float&) {}
 __device__ inline void swap_rows(float&, float&) {}
 #endif
 
+// Orders a wave's LDS accesses for the compiler (the hardware keeps them in
+// order).
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Number of register twiddles a lane keeps for the passes from NS on (the
 // pass whose stride is LNS takes its twiddles from an LDS table instead).
 template <int L, int E, int NS, int LNS, class RL>
@@ -465,7 +474,9 @@ __device__ __forceinline__ void run_passes(const float2 (&in)[E], const float2 (
 #pragma unroll
             for (int m = 0; m < E; ++m)
                 v[m] = lds_a[lds_pad<PAIR>(t + m * T)];
-            if constexpr (!(SWAP && kHaveSwap && T == 64)) {   // one buffer then, see kOneBuffer
+            if constexpr (SWAP && kHaveSwap && T == 64) {   // see kOneBuffer
+                wave_sync();    // the next transform writes what the other lanes read here
+            } else {
                 float2* tmp = lds_a;
                 lds_a = lds_b;
                 lds_b = tmp;
@@ -525,7 +536,7 @@ struct PassFFT {
                                    ? TwiddleCount<L, E, 1, kLNS, Radices<Rs...>>::value : 1;
     // exchange buffers: kLds values, the second from kLdsSplit on
     // (one buffer where one wave makes one exchange per transform: its accesses
-    // execute in order)
+    // execute in order, and the fence behind the reads holds the compiler to it)
     static constexpr bool kOneBuffer = SWAP && kHaveSwap && T == 64;
     static constexpr int kLds = kOneBuffer ? L : 2 * L, kLdsSplit = kOneBuffer ? 0 : L;
     static_assert((1 * ... * Rs) == L, "radices must multiply to L");
@@ -630,15 +641,6 @@ struct PassFFT {
 // took 252 us against 243, since its three exchanges move half as much again
 // through LDS.
 struct WaveSplit {};
-
-// Orders a wave's LDS accesses for the compiler (the hardware keeps them in
-// order).
-__device__ __forceinline__ void wave_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 
 // One 64-bit LDS read or write.  As relaxed atomics, because the compiler would
 // merge neighbouring plain accesses into pairs (ds_read2_b64, ds_write2_b64),

@@ -39,5 +39,16 @@ def build_lds_layout() -> str:
     return out
 
 
+def build_lds_order() -> str:
+    """The transforms alone, with every LDS access recorded (tests/emu/lds_order.cpp)."""
+    out = os.path.join(HERE, "_build", "liblds_order.so")
+    os.makedirs(os.path.dirname(out), exist_ok=True)
+    tmp = out + f".tmp{os.getpid()}"
+    subprocess.run([CXX, "-O1", "-std=c++20", "-fPIC", "-shared", "-pthread", "-I", HERE,
+                    "-x", "c++", os.path.join(HERE, "lds_order.cpp"), "-o", tmp], check=True)
+    os.replace(tmp, out)
+    return out
+
+
 if __name__ == "__main__":
     print(build())

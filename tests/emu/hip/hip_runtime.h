@@ -25,10 +25,12 @@
 #define __align__(n) __attribute__((aligned(n)))
 #define __builtin_nontemporal_store(v, p) (*(p) = (v))
 
+#ifndef EMU_OWN_VECTORS   // a test may bring its own (lds_order.cpp)
 struct float2 { float x, y; };
 inline float2 make_float2(float a, float b) { return float2{a, b}; }
 struct float4 { float x, y, z, w; };
 inline float4 make_float4(float a, float b, float c, float d) { return float4{a, b, c, d}; }
+#endif
 struct double2 { double x, y; };
 inline double2 make_double2(double a, double b) { return double2{a, b}; }
 
@@ -93,14 +95,17 @@ struct EmuIdx { unsigned x = 0, y = 0, z = 0; };
 inline thread_local EmuIdx threadIdx;
 inline EmuIdx blockIdx, gridDim, blockDim;
 inline std::barrier<>* emu_barrier = nullptr;
-inline void __syncthreads() { emu_barrier->arrive_and_wait(); }
+// barriers this thread has passed, for the order checks
+inline thread_local unsigned emu_syncs = 0, emu_wave_syncs = 0;
+inline void __syncthreads() { ++emu_syncs; emu_barrier->arrive_and_wait(); }
 // A wave's lanes run as separate threads here, so a wave-local exchange
 // through LDS needs a barrier over the wave's 64 threads (on the GPU a wave's
 // LDS accesses are in order and the builtin only fences the compiler).
 inline std::vector<std::barrier<>*> emu_wave_barriers;
-inline void emu_wave_barrier() { emu_wave_barriers[threadIdx.x / 64]->arrive_and_wait(); }
+inline void emu_wave_meet() { emu_wave_barriers[threadIdx.x / 64]->arrive_and_wait(); }
+inline void emu_wave_barrier() { ++emu_wave_syncs; emu_wave_meet(); }
 #define __builtin_amdgcn_wave_barrier emu_wave_barrier
-#define __builtin_amdgcn_fence(order, scope) std::atomic_thread_fence(std::memory_order_seq_cst)
+#define __builtin_amdgcn_fence(order, ...) std::atomic_thread_fence(std::memory_order_seq_cst)
 
 using std::max;
 using std::min;
@@ -145,6 +150,28 @@ inline int emu_mov_dpp(int src, int ctrl, int row_mask, int bank_mask, bool boun
 {
     return emu_update_dpp(0, src, ctrl, row_mask, bank_mask, bound_ctrl);
 }
+// The swaps of gfx950 (used where __HIP_DEVICE_COMPILE__ is defined): the upper
+// 32 lanes of a against the lower 32 of b, or each odd row of 16 lanes of a
+// against the even row of b before it.  They order no memory accesses, so they
+// are not counted as barriers.
+struct EmuPair {
+    unsigned v[2];
+    unsigned operator[](int i) const { return v[i]; }
+};
+inline unsigned emu_swap_buf[2][1024];
+inline EmuPair emu_swap(unsigned a, unsigned b, unsigned step)
+{
+    const unsigned t = threadIdx.x;
+    emu_swap_buf[0][t] = a;
+    emu_swap_buf[1][t] = b;
+    emu_wave_meet();
+    const EmuPair r = (t & step) ? EmuPair{{emu_swap_buf[1][t - step], b}}
+                                 : EmuPair{{a, emu_swap_buf[0][t + step]}};
+    emu_wave_meet();
+    return r;
+}
+#define __builtin_amdgcn_permlane32_swap(a, b, fi, bc) emu_swap(a, b, 32)
+#define __builtin_amdgcn_permlane16_swap(a, b, fi, bc) emu_swap(a, b, 16)
 #define __builtin_amdgcn_update_dpp emu_update_dpp
 #define __builtin_amdgcn_mov_dpp emu_mov_dpp
 inline long long clock64() { return 0; }

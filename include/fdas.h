@@ -575,8 +575,12 @@ int fdas_harmonic_sum_batched(const float *planes_dev, const int64_t *offsets_de
  * Folds 2 .. max_fold of every spectrum in one launch after a scan, as
  * fdas_harmonic_sums for one plane: sums_dev is a host array of log2(max_fold)
  * device pointers, fold H laid out as by fdas_harmonic_sum_batched and bitwise
- * the same.  capacity: the bins planes_dev holds (its floats over K), which
- * sizes the launch.  ws_dev: fdas_harmonic_sums_batched_workspace_bytes(nspec) bytes
+ * the same.  capacity: the bins planes_dev holds (its floats over K); it sizes
+ * the launch, and the offsets are clamped to [0, capacity] as by
+ * fdas_correlate_batched, so the call never reads outside the planes whatever
+ * they hold, and never writes outside sums of K_H (capacity / H + nspec) floats
+ * (of spectra that overlap, those that would are left out).
+ * ws_dev: fdas_harmonic_sums_batched_workspace_bytes(nspec) bytes
  * (8-byte aligned, scratch).  Capturable in a graph.
  */
 size_t fdas_harmonic_sums_batched_workspace_bytes(int nspec);
@@ -588,7 +592,9 @@ int fdas_harmonic_sums_batched(const float *planes_dev, const int64_t *offsets_d
  * Candidates of fold H of every spectrum (sums_dev as written by
  * fdas_harmonic_sum_batched for the same offsets, K, H), as
  * fdas_find_candidates; a record's r is the packed bin index offsets[b] + r,
- * which also names the spectrum.  ws_dev as above.
+ * which also names the spectrum.  ws_dev: fdas_harmonic_batched_workspace_bytes
+ * bytes.  The offsets are taken as they are: non-decreasing, with sums_dev
+ * holding the folds they describe.
  */
 int fdas_find_candidates_batched(const float *sums_dev, const int64_t *offsets_dev, int nspec,
                                  int K, int H, float threshold, fdas_candidate *out_dev,

@@ -947,7 +947,7 @@ size_t fdas_harmonic_sums_batched_workspace_bytes(int nspec)
 {
     if (nspec < 0 || nspec > kMaxSpectra)
         return 0;
-    const size_t b = 7 * ((size_t)nspec + 1) * sizeof(int64_t);
+    const size_t b = 9 * ((size_t)nspec + 1) * sizeof(int64_t);
     return (b + 255) & ~(size_t)255;
 }
 

@@ -19,6 +19,17 @@ std::complex<double> response(double q, double z);
 // taps [K][Mt], equal bit for bit to response() rounded to FP32.
 hipError_t launch_templates(double dz, int K, int Mt, bool half, float2* taps, hipStream_t s);
 
+// Spectrum b's first packed bin and length, clamped to [0, cap].
+__device__ __forceinline__ void spec_range(const int64_t* __restrict__ offsets, int b, int64_t cap,
+                                           int64_t& off, int64_t& n)
+{
+    int64_t o0 = offsets[b], o1 = offsets[b + 1];
+    o0 = o0 < 0 ? 0 : (o0 > cap ? cap : o0);
+    o1 = o1 < o0 ? o0 : (o1 > cap ? cap : o1);
+    off = o0;
+    n = o1 - o0;
+}
+
 // Bank rows H_z and the twiddle row for segment length L.
 hipError_t launch_prepare_bank(const float2* taps, int K, int M, int L, float2* bank,
                                hipStream_t s);
@@ -101,7 +112,7 @@ hipError_t launch_harmonic_sum(const float* plane, int64_t N, int K, int H, cons
 hipError_t launch_fold_chain(const float* plane, int64_t N, int K, const float* prev,
                              int log_first, int log_last, float* const* sums, hipStream_t s);
 // Folds 2 .. 2^log_last of every spectrum of a batch of at most `capacity` bins;
-// pre holds (log_last + 1) (nspec + 1) int64.
+// pre holds (log_last + 3) (nspec + 1) int64.
 hipError_t launch_fold_chain_batched(const float* planes, const int64_t* offsets, int nspec,
                                      int64_t capacity, int K, int log_last, float* const* sums,
                                      int64_t* pre, hipStream_t s);

@@ -579,17 +579,6 @@ __global__ __launch_bounds__(Fwd<L>::T, 2) void forward_kernel(
 
 constexpr int kScanThreads = 1024;
 
-// Spectrum b's first packed bin and length, clamped to [0, cap].
-__device__ __forceinline__ void spec_range(const int64_t* __restrict__ offsets, int b, int64_t cap,
-                                           int64_t& off, int64_t& n)
-{
-    int64_t o0 = offsets[b], o1 = offsets[b + 1];
-    o0 = o0 < 0 ? 0 : (o0 > cap ? cap : o0);
-    o1 = o1 < o0 ? o0 : (o1 > cap ? cap : o1);
-    off = o0;
-    n = o1 - o0;
-}
-
 // segpre[b + 1] = sum over b' <= b of ceil(N_b' / B) (segments of length B,
 // or the adjoint's windows, which have the same count).
 __global__ __launch_bounds__(kScanThreads) void segment_scan_kernel(

@@ -98,25 +98,45 @@ __device__ __forceinline__ void fold_item(int64_t l, int P, int rows, int& p, in
     row = (int)(i - q * (uint32_t)rows);
 }
 
-// Adds harmonics H/2 + 1 .. H of columns r + 64 j to s, in that order (FULL:
+// Adds harmonics H/2 + 1 .. H of columns r0 + t + 64 j to s, in that order (FULL:
 // all of them lie below NH).  Harmonic h is at h (dk N + r) from the centre row.
+//
+// The last chunk of a row, from 32 harmonics on: columns past NH read the last one's
+// values (their sums are not stored), so that no load waits for a test of its own,
+// and addresses are a scalar base and a 32-bit offset per lane.  Tested and addressed
+// one by one these loads took more registers than there are (166 spilled) and ran
+// one after another: the 64-harmonic fold of a 21 x 5000 plane 14.8 us, now 3.9,
+// folds 2..64 of 201 x 300000 121 us, now 97; up to 16 harmonics the same either way.
 template <int H, bool FULL>
 __device__ __forceinline__ void fold_add(const float* __restrict__ centre, int64_t N, int64_t dk,
-                                         int64_t r, int64_t NH, float (&s)[kFoldPerLane])
+                                         int64_t r0, int t, int64_t NH, float (&s)[kFoldPerLane])
 {
     constexpr int FIRST = H == 1 ? 1 : H / 2 + 1;
     constexpr int COUNT = H == 1 ? 1 : H / 2;
     constexpr int GROUP = COUNT < kFoldGroup ? COUNT : kFoldGroup;
+    constexpr bool LAST_VALUES = !FULL && H >= 32;
+    const int64_t r = r0 + t;
+    uint32_t at[kFoldPerLane];            // column offsets of LAST_VALUES, in bytes
+    if constexpr (LAST_VALUES) {
+#pragma unroll
+        for (int j = 0; j < kFoldPerLane; ++j)
+            at[j] = 4u * min((uint32_t)(t + j * kFoldThreads), (uint32_t)(NH - 1 - r0));
+    }
 #pragma unroll
     for (int g = 0; g < COUNT; g += GROUP) {
         float v[GROUP][kFoldPerLane];
 #pragma unroll
         for (int i = 0; i < GROUP; ++i) {
             const int h = FIRST + g + i;
-            const float* row = centre + h * (dk * N + r);
+            const float* row = centre + h * (dk * N + (LAST_VALUES ? r0 : r));
 #pragma unroll
-            for (int j = 0; j < kFoldPerLane; ++j)
-                v[i][j] = FULL || r + j * kFoldThreads < NH ? row[h * j * kFoldThreads] : 0.f;
+            for (int j = 0; j < kFoldPerLane; ++j) {
+                if constexpr (LAST_VALUES)
+                    v[i][j] = *reinterpret_cast<const float*>(
+                        reinterpret_cast<const char*>(row) + (uint32_t)h * at[j]);
+                else
+                    v[i][j] = FULL || r + j * kFoldThreads < NH ? row[h * j * kFoldThreads] : 0.f;
+            }
         }
 #pragma unroll
         for (int i = 0; i < GROUP; ++i)
@@ -139,7 +159,7 @@ __device__ __forceinline__ void fold_put(float* __restrict__ o, int64_t r, int64
 // harmonics and store the sums where the fold is wanted; false ends the chain.
 template <int LOG>
 __device__ __forceinline__ bool fold_stage(const float* __restrict__ centre, int64_t N, int c,
-                                           int64_t dk, int64_t r0, int64_t r, const FoldOut& out,
+                                           int64_t dk, int64_t r0, int t, const FoldOut& out,
                                            float (&s)[kFoldPerLane])
 {
     constexpr int H = 1 << LOG;
@@ -148,11 +168,11 @@ __device__ __forceinline__ bool fold_stage(const float* __restrict__ centre, int
     if (dk > kc || -dk > kc || r0 >= NH)
         return false;                 // uniform in the wave
     if (r0 + kFoldCols <= NH)
-        fold_add<H, true>(centre, N, dk, r, NH, s);
+        fold_add<H, true>(centre, N, dk, r0, t, NH, s);
     else
-        fold_add<H, false>(centre, N, dk, r, NH, s);
+        fold_add<H, false>(centre, N, dk, r0, t, NH, s);
     if (out.p[LOG] != nullptr)
-        fold_put(out.p[LOG] + (dk + kc) * NH + r, r, NH, s);
+        fold_put(out.p[LOG] + (dk + kc) * NH + r0 + t, r0 + t, NH, s);
     return true;
 }
 
@@ -181,14 +201,14 @@ __device__ __forceinline__ void fold_chain(const float* __restrict__ plane, int6
                 s[j] = p[j * kFoldThreads];
         log = log_first;
     }
-    if (log <= 0 && !fold_stage<0>(centre, N, c, dk, r0, r, out, s)) return;
-    if (log <= 1 && (log_last < 1 || !fold_stage<1>(centre, N, c, dk, r0, r, out, s))) return;
-    if (log <= 2 && (log_last < 2 || !fold_stage<2>(centre, N, c, dk, r0, r, out, s))) return;
-    if (log <= 3 && (log_last < 3 || !fold_stage<3>(centre, N, c, dk, r0, r, out, s))) return;
-    if (log <= 4 && (log_last < 4 || !fold_stage<4>(centre, N, c, dk, r0, r, out, s))) return;
-    if (log <= 5 && (log_last < 5 || !fold_stage<5>(centre, N, c, dk, r0, r, out, s))) return;
+    if (log <= 0 && !fold_stage<0>(centre, N, c, dk, r0, t, out, s)) return;
+    if (log <= 1 && (log_last < 1 || !fold_stage<1>(centre, N, c, dk, r0, t, out, s))) return;
+    if (log <= 2 && (log_last < 2 || !fold_stage<2>(centre, N, c, dk, r0, t, out, s))) return;
+    if (log <= 3 && (log_last < 3 || !fold_stage<3>(centre, N, c, dk, r0, t, out, s))) return;
+    if (log <= 4 && (log_last < 4 || !fold_stage<4>(centre, N, c, dk, r0, t, out, s))) return;
+    if (log <= 5 && (log_last < 5 || !fold_stage<5>(centre, N, c, dk, r0, t, out, s))) return;
     if (log <= 6 && log_last >= 6)
-        fold_stage<6>(centre, N, c, dk, r0, r, out, s);
+        fold_stage<6>(centre, N, c, dk, r0, t, out, s);
 }
 
 // One wave per (chunk, row of the first fold): workgroup b takes row b mod KH
@@ -374,8 +394,7 @@ __device__ __forceinline__ int64_t fold_columns(int64_t N, int log)
 // row i <= folds the columns of fold 2^(log + i - 1).  A workgroup
 // beyond those writes the row behind them, the prefix of the spectra's lengths, and the
 // next, their starts.  Offsets are clamped to [0, cap].  `zero` (or NULL) is set to 0.
-// A chain of dependent steps: 1024 lanes take a tenth of the steps per spectrum that 256
-// took (folds 2 of 3000 spectra of 200 bins, 7 rows: 28.9 -> 20.8 us).
+// A chain of dependent steps: 1024 lanes take a third of the steps that 256 took (folds 2 of 3000 spectra of 200 bins, 7 rows: 28.9 -> 20.8 us).
 constexpr int kFoldScanThreads = 1024;
 
 __global__ __launch_bounds__(kFoldScanThreads) void fold_scan_kernel(
@@ -430,10 +449,10 @@ __global__ __launch_bounds__(kFoldScanThreads) void fold_scan_kernel(
 // One wave per work item (more waves than the host's bound on them stride on),
 // so the waves of the moment work on neighbouring chunks of one spectrum.  Fold
 // 2^i of spectrum b lies at out.p[i] + KH pre[i][b].  The spectra are those of the
-// offsets clamped to the bins the planes hold, from the scan's last two rows (clamped
-// here, wave by wave, the same took a tenth of the call's time: 64.1 -> 72.5 us for fold 2 of 85 x 2^20); overlapping ones whose
-// lengths add up to more than cap, and so their folds to more than cap / 2^i + nspec
-// columns, are left out.  Measured, 8 spectra of
+// offsets clamped to the bins the planes hold, from the scan's last two rows
+// (clamped here, wave by wave, the same took fold 2 of 85 x 2^20 from 64.1 to 72.5
+// us); overlapping ones whose lengths add up to more than cap, and so their folds
+// to more than cap / 2^i + nspec columns, are left out.  Measured, 8 spectra of
 // 131073 bins, 41 rows, folds 2..16: 51 us; 64 us as one launch per fold, and
 // 83 us with persistent waves, which paid for a new spectrum nearly every item.
 __global__ __launch_bounds__(kFoldThreads, 8) void fold_chain_batched_kernel(

@@ -227,6 +227,83 @@ __global__ __launch_bounds__(kFoldThreads, 8) void fold_chain_kernel(
                threadIdx.x, prev, log_first, log_last, out);
 }
 
+// ---- one fold -----------------------------------------------------------------
+//
+// One row of the H-fold sum per blockIdx.y, kHarmCols columns per
+// blockIdx.x: lane t takes columns t + kHarmThreads j, j < kHarmCols /
+// kHarmThreads, so each load instruction is coalesced and every lane keeps
+// several independent gathers in flight.  With prev (the H/2-fold, KHp x
+// NHp), the sum starts from it and adds harmonics H/2 + 1 .. H; without, it
+// adds 1 .. H from zero.
+constexpr int kHarmPerLane = 4;
+constexpr int kHarmCols = kHarmThreads * kHarmPerLane;
+
+__global__ __launch_bounds__(kHarmThreads) void harmonic_sum_kernel(
+    const float* __restrict__ plane, int64_t N, int K, int H, const float* __restrict__ prev,
+    int64_t NHp, int KHp, float* __restrict__ out, int64_t NH, int KH)
+{
+    const int64_t r0 = (int64_t)blockIdx.x * kHarmCols + threadIdx.x;
+    const int c = (K - 1) / 2;
+    const int krow = blockIdx.y;                       // row of the fold
+    const int dk = krow - (KH - 1) / 2;                // k - c of the fundamental
+    float s[kHarmPerLane];
+    bool in[kHarmPerLane];
+#pragma unroll
+    for (int j = 0; j < kHarmPerLane; ++j) {
+        in[j] = r0 + (int64_t)j * kHarmThreads < NH;
+        s[j] = 0.f;
+    }
+    int h0 = 1;
+    if (prev != nullptr) {
+        const float* p = prev + (int64_t)(dk + (KHp - 1) / 2) * NHp + r0;
+#pragma unroll
+        for (int j = 0; j < kHarmPerLane; ++j)
+            if (in[j])
+                s[j] = p[(int64_t)j * kHarmThreads];
+        h0 = H / 2 + 1;
+    }
+    for (int h = h0; h <= H; ++h) {
+        const float* row = plane + (int64_t)(c + h * dk) * N + (int64_t)h * r0;
+#pragma unroll
+        for (int j = 0; j < kHarmPerLane; ++j)
+            if (in[j])
+                s[j] += row[(int64_t)h * j * kHarmThreads];
+    }
+    float* o = out + (int64_t)krow * NH + r0;
+#pragma unroll
+    for (int j = 0; j < kHarmPerLane; ++j)
+        if (in[j])
+            o[(int64_t)j * kHarmThreads] = s[j];
+}
+
+// One fold goes to this kernel or, with one stage, to fold_chain_kernel, whose lanes
+// keep more loads in flight but whose order of the chunks is made for chains.
+// Measured, this kernel -> the chain's (us):
+//   H = 1: 85 x 20000 4.5 -> 5.3, 121 x 35391 8.6 -> 8.9, 201 x 44772 15.3 -> 14.4, 85 x
+//   2^20 170 -> 141;
+//   H = 2: 61 x 17537 3.7 -> 3.6, 61 x 83834 4.7 -> 5.3, 121 x 73983 9.0 -> 7.1, 85 x 2^20
+//   75 -> 57; one row of 2065151 columns 5.7 -> 6.6;
+//   H = 4 to 16 on top of the fold below: 85 x 2^22 134 -> 156, 106 -> 112, 79 -> 82,
+//   85 x 2^20 29.5 -> 30.4, 24.4 -> 24.9, 19.8 -> 21; where this kernel's workgroups are
+//   fewer than the CUs, 41 x 131073 (H = 8, 16) 4.7 -> 3.7, 6.7 -> 3.8; 4-fold of short
+//   rows, 201 x 29908 4.0 -> 4.2 but 1025 x 30000 14.5 -> 12.6;
+//   H = 4, 8 from the plane: 85 x 2^20 39 -> 32, 34 -> 30; 85 x 2^22 153 -> 161, 124 ->
+//   130; 16: 29 -> 26, 103 -> 99;
+//   H = 32 and 64: 85 x 2^22 91 -> 88, 49 -> 17, 1025 x 30000 24 -> 9, 25 -> 12.5.
+bool one_fold_by_chain(int64_t N, int K, int H, int64_t NH, int KH, bool prev)
+{
+    const int64_t points = N * K, blocks = (NH + kHarmCols - 1) / kHarmCols * KH;
+    if (H == 1)
+        return points >= 1 << 23;
+    if (H == 2)
+        return points < 1 << 21 || (points >= 1 << 23 && KH > 1);
+    if (H >= 32)
+        return true;
+    if (!prev)
+        return H == 16 || points < (int64_t)1 << 28;
+    return blocks < 256 || (H == 4 && NH < 1 << 14 && points >= 1 << 24);
+}
+
 __global__ void zero_count_kernel(unsigned* __restrict__ count)
 {
     if (threadIdx.x == 0)
@@ -582,10 +659,23 @@ hipError_t launch_fold_chain(const float* plane, int64_t N, int K, const float* 
 hipError_t launch_harmonic_sum(const float* plane, int64_t N, int K, int H, const float* prev,
                                float* out, hipStream_t s)
 {
-    int log = 0;
-    while ((1 << log) < H)
-        ++log;
-    return launch_fold_chain(plane, N, K, prev, log, log, &out, s);
+    int KH = 0, KHp = 0;
+    int64_t NH = 0, NHp = 0;
+    harmonic_shape(N, K, H, &KH, &NH);
+    if (prev != nullptr)
+        harmonic_shape(N, K, H / 2, &KHp, &NHp);
+    if (NH == 0)
+        return hipSuccess;
+    if (one_fold_by_chain(N, K, H, NH, KH, prev != nullptr)) {
+        int log = 0;
+        while ((1 << log) < H)
+            ++log;
+        return launch_fold_chain(plane, N, K, prev, log, log, &out, s);
+    }
+    const dim3 grid((unsigned)((NH + kHarmCols - 1) / kHarmCols), (unsigned)KH);
+    hipLaunchKernelGGL(harmonic_sum_kernel, grid, dim3(kHarmThreads), 0, s, plane, N, K, H, prev,
+                       NHp, KHp, out, NH, KH);
+    return hipGetLastError();
 }
 
 hipError_t launch_candidates(const float* S, int64_t N, int K, int H, float threshold,

@@ -310,22 +310,22 @@ __global__ void zero_count_kernel(unsigned* __restrict__ count)
         *count = 0u;
 }
 
-// Whether v = S[k][r] is >= each of its neighbours inside the fold.
+// Whether v = S[k][r] is >= each of its neighbours inside the fold.  All eight are read
+// at once; one outside the fold is replaced by the nearest point inside, another
+// neighbour or v itself.
 __device__ __forceinline__ bool is_peak(const float* __restrict__ S, int64_t NH, int KH, int k,
                                         int64_t r, float v)
 {
+    const float* row = S + (int64_t)k * NH;
+    const float* up = k > 0 ? row - NH : row;
+    const float* down = k + 1 < KH ? row + NH : row;
+    const int64_t left = r > 0 ? r - 1 : r, right = r + 1 < NH ? r + 1 : r;
+    const float near[8] = {up[left],   up[r],      up[right], row[left],
+                           row[right], down[left], down[r],   down[right]};
     bool peak = true;
-    for (int a = -1; a <= 1; ++a) {
-        const int kk = k + a;
-        if (kk < 0 || kk >= KH)
-            continue;
-        for (int b = -1; b <= 1; ++b) {
-            const int64_t rr = r + b;
-            if ((a == 0 && b == 0) || rr < 0 || rr >= NH)
-                continue;
-            peak = peak && v >= S[(int64_t)kk * NH + rr];
-        }
-    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+        peak = peak && v >= near[i];
     return peak;
 }
 
@@ -344,14 +344,18 @@ __device__ __forceinline__ void put_candidate(fdas_candidate* __restrict__ out, 
 }
 
 // Peaks of one fold: S > threshold and S >= each neighbour inside the fold.
-// Bound by reading the fold once; a lane keeps kCandPerLane loads in flight
-// (lane t takes columns t + kHarmThreads j), which is what the rate hangs on:
-// 57 us for 85 x 2^20 (6.3 TB/s), 107 us with one.
+// Bound by reading the fold once; a lane keeps PER loads in flight (lane t takes
+// columns t + kHarmThreads j), which is what the rate hangs on: 57 us for 85 x 2^20
+// with 8 (6.3 TB/s), 107 us with one.  Where points pass the threshold a lane looks at
+// its columns one after the other, and the last waves' looks are the tail of the
+// call: with the neighbours read one by one 82 -> 87 us for 10^4 peaks in 201 x 300000
+// (8 columns per lane against one), all at once 81 us.
 constexpr int kCandPerLane = 8;
 constexpr int kCandCols = kHarmThreads * kCandPerLane;
 
-// Columns c0 .. c0 + kCandCols of row k of one fold; a candidate's r is reported
+// Columns c0 .. c0 + kHarmThreads PER of row k of one fold; a candidate's r is reported
 // from column r_at on.
+template <int PER>
 __device__ __forceinline__ void find_peaks(const float* __restrict__ S, int64_t NH, int KH, int k,
                                            int64_t c0, float threshold, int row0, int64_t r_at,
                                            fdas_candidate* __restrict__ out, int capacity,
@@ -359,35 +363,36 @@ __device__ __forceinline__ void find_peaks(const float* __restrict__ S, int64_t 
 {
     const int64_t r = c0 + threadIdx.x;
     const float* row = S + (int64_t)k * NH + r;
-    float v[kCandPerLane];
-    if (c0 + kCandCols <= NH) {
+    float v[PER];
+    if (c0 + kHarmThreads * PER <= NH) {
 #pragma unroll
-        for (int j = 0; j < kCandPerLane; ++j)
+        for (int j = 0; j < PER; ++j)
             v[j] = row[j * kHarmThreads];
     } else {
         // a column outside the fold gets the threshold itself: no candidate
 #pragma unroll
-        for (int j = 0; j < kCandPerLane; ++j)
+        for (int j = 0; j < PER; ++j)
             v[j] = r + j * kHarmThreads < NH ? row[j * kHarmThreads] : threshold;
     }
     bool any = false;
 #pragma unroll
-    for (int j = 0; j < kCandPerLane; ++j)
+    for (int j = 0; j < PER; ++j)
         any = any || v[j] > threshold;
     if (!any)
         return;
 #pragma unroll
-    for (int j = 0; j < kCandPerLane; ++j)
+    for (int j = 0; j < PER; ++j)
         if (v[j] > threshold && is_peak(S, NH, KH, k, r + j * kHarmThreads, v[j]))
             put_candidate(out, capacity, count, r_at + r + j * kHarmThreads, row0 + k, v[j]);
 }
 
+template <int PER>
 __global__ __launch_bounds__(kHarmThreads) void candidates_kernel(
     const float* __restrict__ S, int64_t NH, int KH, float threshold, int row0,
     fdas_candidate* __restrict__ out, int capacity, unsigned* __restrict__ count)
 {
-    find_peaks(S, NH, KH, blockIdx.y, (int64_t)blockIdx.x * kCandCols, threshold, row0, 0, out,
-               capacity, count);
+    find_peaks<PER>(S, NH, KH, blockIdx.y, (int64_t)blockIdx.x * (kHarmThreads * PER), threshold,
+                    row0, 0, out, capacity, count);
 }
 
 // ---- batched: the planes of fdas_correlate_batched (plane b at K offsets[b],
@@ -613,8 +618,9 @@ __global__ __launch_bounds__(kHarmThreads) void candidates_batched_kernel(
     for (int64_t g = blockIdx.x; g < total; g += gridDim.x) {
         const int b = column_spectrum(pre, nspec, g);
         const int64_t off = offsets[b], NH = fold_columns(offsets[b + 1] - off, log);
-        find_peaks(sums + (int64_t)KH * pre[nspec + 1 + b], NH, KH, blockIdx.y,
-                   (g - pre[b]) * kCandCols, threshold, row0, off, out, capacity, count);
+        find_peaks<kCandPerLane>(sums + (int64_t)KH * pre[nspec + 1 + b], NH, KH, blockIdx.y,
+                                 (g - pre[b]) * kCandCols, threshold, row0, off, out, capacity,
+                                 count);
     }
 }
 
@@ -689,9 +695,19 @@ hipError_t launch_candidates(const float* S, int64_t N, int K, int H, float thre
     if (e != hipSuccess || NH == 0)
         return e;
     const int row0 = (K - 1) / 2 - (KH - 1) / 2;
-    const dim3 grid((unsigned)((NH + kCandCols - 1) / kCandCols), (unsigned)KH);
-    hipLaunchKernelGGL(candidates_kernel, grid, dim3(kHarmThreads), 0, s, S, NH, KH, threshold,
-                       row0, out, capacity, count);
+    // One column per lane while that gives no more workgroups than run at once (8 per
+    // CU): there is nothing to wait for but the looks themselves.  Every local maximum of
+    // 1 x 5000 4.9 us against 8.5, of the 32-fold of 41 x 131073 4.7 against 9.1.
+    const int64_t blocks = (NH + kHarmThreads - 1) / kHarmThreads;
+    if (blocks * KH <= 2048)
+        hipLaunchKernelGGL((candidates_kernel<1>), dim3((unsigned)blocks, (unsigned)KH),
+                           dim3(kHarmThreads), 0, s, S, NH, KH, threshold, row0, out, capacity,
+                           count);
+    else
+        hipLaunchKernelGGL((candidates_kernel<kCandPerLane>),
+                           dim3((unsigned)((NH + kCandCols - 1) / kCandCols), (unsigned)KH),
+                           dim3(kHarmThreads), 0, s, S, NH, KH, threshold, row0, out, capacity,
+                           count);
     return hipGetLastError();
 }
 

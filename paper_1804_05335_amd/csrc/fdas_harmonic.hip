@@ -608,17 +608,38 @@ __global__ __launch_bounds__(kHarmThreads) void harmonic_batched_kernel(
 // index offsets[b] + r, which names the spectrum too.  Workgroup row y takes fold
 // row y, its workgroups stride over the chunks of kCandCols columns that pre row 0
 // counts (a spectrum found per chunk; one found per column and lane took 67 us for
-// 8 x 41 x 131073, this 28 us).
+// 8 x 41 x 131073, this 28 us).  Chunks that hold under an eighth of their columns, and
+// more of them than workgroups, each pay the search for next to nothing: there every
+// lane takes one column of one spectrum and walks its rows (3000 spectra of 200 bins, 7
+// rows, 420 peaks: 49 -> 21 us, all 467000 peaks 901 -> 759; 300 of 128 columns, a
+// chunk for every workgroup, 8.8 us by chunks and 10.5 by lanes).
 __global__ __launch_bounds__(kHarmThreads) void candidates_batched_kernel(
     const float* __restrict__ sums, const int64_t* __restrict__ offsets, int nspec, int log,
     const int64_t* __restrict__ pre, int KH, float threshold, int row0,
     fdas_candidate* __restrict__ out, int capacity, unsigned* __restrict__ count)
 {
     const int64_t total = pre[nspec];
+    const int64_t* const column = pre + nspec + 1;
+    if (total > gridDim.x && column[nspec] < total * kHarmThreads) {
+        const int64_t lanes = (int64_t)gridDim.x * gridDim.y * kHarmThreads;
+        for (int64_t g = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * kHarmThreads + threadIdx.x;
+             g < column[nspec]; g += lanes) {
+            const int b = column_spectrum(column, nspec, g);
+            const int64_t off = offsets[b], NH = fold_columns(offsets[b + 1] - off, log);
+            const int64_t r = g - column[b];
+            const float* S = sums + (int64_t)KH * column[b];
+            for (int k = 0; k < KH; ++k) {
+                const float v = S[(int64_t)k * NH + r];
+                if (v > threshold && is_peak(S, NH, KH, k, r, v))
+                    put_candidate(out, capacity, count, off + r, row0 + k, v);
+            }
+        }
+        return;
+    }
     for (int64_t g = blockIdx.x; g < total; g += gridDim.x) {
         const int b = column_spectrum(pre, nspec, g);
         const int64_t off = offsets[b], NH = fold_columns(offsets[b + 1] - off, log);
-        find_peaks<kCandPerLane>(sums + (int64_t)KH * pre[nspec + 1 + b], NH, KH, blockIdx.y,
+        find_peaks<kCandPerLane>(sums + (int64_t)KH * column[b], NH, KH, blockIdx.y,
                                  (g - pre[b]) * kCandCols, threshold, row0, off, out, capacity,
                                  count);
     }

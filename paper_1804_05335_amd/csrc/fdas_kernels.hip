@@ -516,12 +516,12 @@ struct Fwd {
 };
 
 // Work partition of the persistent kernels: the flattened (segment,
-// template) items [0, total) are split into gridDim.x contiguous ranges, one
-// per workgroup, so every workgroup gets the same number of templates (+-1)
+// template) items [0, total) are split into P contiguous ranges, one per
+// workgroup, so every workgroup gets the same number of templates (+-1)
 // and recomputes a window FFT only where its range enters a segment.
-__device__ __forceinline__ void item_range(int64_t total, int64_t& i0, int64_t& i1)
+__device__ __forceinline__ void item_range(int64_t total, int64_t P, int64_t& i0, int64_t& i1)
 {
-    const int64_t P = gridDim.x, w = blockIdx.x;
+    const int64_t w = blockIdx.x;
     i0 = total * w / P;
     i1 = total * (w + 1) / P;
 }
@@ -540,7 +540,7 @@ __global__ __launch_bounds__(Fwd<L>::T, 2) void forward_kernel(
     __shared__ float2 twl[W::F::kLdsTwAlloc];
     __shared__ __align__(16) float2 edge[IB ? W::kEdgeAlloc : 1];   // interbinning
     int64_t i, i1;
-    item_range(nseg * K, i, i1);
+    item_range(nseg * K, gridDim.x, i, i1);
     if (i >= i1)
         return;     // uniform across the workgroup, before any barrier
     const int t = W::F::place(threadIdx.x);
@@ -640,7 +640,14 @@ __global__ __launch_bounds__((Fwd<L, E>::T), 2) void batched_kernel(
     __shared__ __align__(16) float2 lds[W::F::kLds];
     __shared__ float2 twl[W::F::kLdsTwAlloc];
     int64_t i, i1;
-    item_range(segpre[nspec] * K, i, i1);
+    // Fewer items than workgroups, which only the device knows: the first ones take one
+    // each.  Spread over the whole grid they shared CUs while others idled: 168 items,
+    // E = 8, L = 4096, grid 512: 17.1 us, so 12.7; L = 2048, 1024: 15.9 and 10.1; E = 16, L =
+    // 2048, 512: 14.6 and 10.9.
+    const int64_t items = segpre[nspec] * K, P = min<int64_t>(gridDim.x, items);
+    if (blockIdx.x >= P)
+        return;
+    item_range(items, P, i, i1);
     if (i >= i1)
         return;
     const int t = W::F::place(threadIdx.x);
@@ -1269,7 +1276,15 @@ template <int L, int E, int DEAD>
 static hipError_t resident_batched_LD(int* grid)
 {
     static std::atomic<int> cache[64];
-    return resident_grid(batched_kernel<L, E, DEAD>, Fwd<L, E>::T, cache, grid);
+    const hipError_t e = resident_grid(batched_kernel<L, E, DEAD>, Fwd<L, E>::T, cache, grid);
+    // Five of the eight workgroups that fit a CU: with all of them at work the 960 or 896
+    // columns of each, in rows of any alignment, leave more half-written lines than
+    // the caches hold until a neighbour completes them.  Spectra of odd length, K = 85,
+    // M = 64: 2048 workgroups 97.8 us, 1280 83.7 (1536 of the plan before 87.3); of even
+    // length 81.1 and 85.0 (88.9).
+    if (L == 1024 && E == 8 && DEAD == 0)
+        *grid = *grid * 5 / 8;
+    return e;
 }
 
 template <int L, int E>

@@ -237,7 +237,19 @@ hipError_t launch_prepare_bank(const float2* taps, int K, int M, int L, float2* 
 // below L = 1024, whose one-wave workgroups pay more for the branch than they
 // gain (300001 bins, K = 85, M = 64, L = 512: 39.1 -> 41.5 us), nor at L = 8192,
 // where one workgroup fills the CU and the two-bin kernel has no register to
-// spare for the count (709 -> 1020 us).
+// spare for the count (709 -> 1020 us).  At L = 2048 and 4096 the half-bin, symmetric
+// and two-bin kernels also run without (TURNS false) where a workgroup has fewer than
+// kTurnItems templates: there is nothing to catch up with, and the branches cost the
+// half-bin plane of 13476 bins (K = 121, M = 512, L = 2048) 13.6 -> 13.8 us, the
+// two-bin plane at L = 4096 16.9 -> 17.2 (two spilled registers).  The plain kernel and
+// the two-bin kernel with no dead slots at L = 4096, which turns leave with fewer spills,
+// are the faster with turns there too (13.8 -> 13.4 and 20.5 -> 18.1 us).
+// Kernels of other streams on the same CU run at priority 0 and yield to the waves
+// above it.  Measured beside the plane of 2^21 bins without turns -> with: a copy of 64 MB
+// 33.7 -> 34.7 us a call, a candidate search of 85 x 2^18 71.5 -> 58.3, an addition of 4096
+// values 4.4 -> 4.7; beside the half-bin plane 40.2 -> 41.9, 63.5 -> 57.3, 4.5 -> 4.6.
+constexpr int kTurnItems = 4;
+
 __device__ __forceinline__ void give_way(int n)
 {
 #ifdef __HIP_DEVICE_COMPILE__   // the host pass and the CPU emulation have no priorities
@@ -269,6 +281,7 @@ constexpr float kQuarterPi2 = 0.61685027506808491368f;   // (pi/4)^2, interbinni
 // workgroup's consecutive work needs no extra barrier.
 template <int L, int EV = Geometry<L>::E, bool IB_PLAN = false>
 struct Fwd {
+    static constexpr bool kTurns = L >= 1024 && L <= 4096;    // see give_way
     static constexpr int E = EV;
     using F = FFT<L, E, typename std::conditional_t<IB_PLAN && L == 8192, Plan<L, E>, SwapPlan<L, E>>::R>;
     static constexpr int T = F::T;
@@ -351,7 +364,7 @@ struct Fwd {
     // any lane (positions below M/2 or from L - M/2 on, which needs
     // M/2 >= DEAD T); their power and stores are skipped, so the compiler
     // also drops the last butterfly operations that feed only them.
-    template <bool IB, bool SYM = false, bool DUAL = false, int DEAD = 0>
+    template <bool IB, bool SYM = false, bool DUAL = false, int DEAD = 0, bool TURNS = kTurns>
     __device__ static void item(const float2* __restrict__ spec, int64_t N,
                                 const float2* __restrict__ bank, int K, int M, int64_t s, int z0,
                                 int z1, float* __restrict__ plane, const typename F::TW& tw,
@@ -371,7 +384,7 @@ struct Fwd {
         // bank, z < c), consumed reversed and conjugated.
         auto one = [&](int z, auto mir_tag) {
             constexpr bool MIR = decltype(mir_tag)::value;
-            if constexpr (L >= 1024 && L <= 4096)
+            if constexpr (TURNS)
                 give_way(turn++);
             float2 v[E];
             const int znext = z + 1 == K ? 0 : z + 1;
@@ -530,7 +543,7 @@ __device__ __forceinline__ void item_range(int64_t total, int64_t P, int64_t& i0
 // interbinned plane ([K][2N]) instead of the plain one ([K][N]); SYM a bank
 // that stores only the z >= 0 rows; DUAL adds the half-bin bank bank2 and
 // writes interleaved [K][2N] pairs.
-template <int L, bool IB, bool SYM, bool DUAL, int DEAD>
+template <int L, bool IB, bool SYM, bool DUAL, int DEAD, bool TURNS>
 __global__ __launch_bounds__(Fwd<L>::T, 2) void forward_kernel(
     const float2* __restrict__ spec, int64_t N, const float2* __restrict__ bank, int K, int M,
     int64_t nseg, float* __restrict__ plane, const float2* __restrict__ bank2)
@@ -557,7 +570,7 @@ __global__ __launch_bounds__(Fwd<L>::T, 2) void forward_kernel(
         const int64_t s = i / K;
         const int zs = (int)(i - s * K);
         const int ze = (int)min<int64_t>(K, zs + (i1 - i));
-        W::template item<IB, SYM, DUAL, DEAD>(spec, N, bank, K, M, s, zs, ze, plane, tw, la, lb,
+        W::template item<IB, SYM, DUAL, DEAD, TURNS>(spec, N, bank, K, M, s, zs, ze, plane, tw, la, lb,
                                                t, H, turn, bank2, edge);
         i += ze - zs;
     }
@@ -630,7 +643,7 @@ __device__ __forceinline__ int owner(const int64_t* __restrict__ segpre, int nsp
     return lo;
 }
 
-template <int L, int E, int DEAD>
+template <int L, int E, int DEAD, bool TURNS>
 __global__ __launch_bounds__((Fwd<L, E>::T), 2) void batched_kernel(
     const float2* __restrict__ specs, const int64_t* __restrict__ offsets,
     const int64_t* __restrict__ segpre, int nspec, int64_t cap, const float2* __restrict__ bank,
@@ -666,7 +679,7 @@ __global__ __launch_bounds__((Fwd<L, E>::T), 2) void batched_kernel(
         const int b = owner(segpre, nspec, tile);
         int64_t off, Nb;
         spec_range(offsets, b, cap, off, Nb);
-        W::template item<false, false, false, DEAD>(specs + off, Nb, bank, K, M,
+        W::template item<false, false, false, DEAD, TURNS>(specs + off, Nb, bank, K, M,
                                                     tile - segpre[b], zs, ze,
                                                     planes + (int64_t)K * off, tw, la, lb, t, H,
                                                     turn);
@@ -1193,23 +1206,35 @@ static hipError_t resident_grid(Kern kernel, int threads, std::atomic<int>* cach
     return hipSuccess;
 }
 
+template <int L, bool IB, bool SYM, bool DUAL, int DEAD, bool TURNS>
+static hipError_t resident_forward(int* grid)
+{
+    static std::atomic<int> cache[64];
+    return resident_grid(forward_kernel<L, IB, SYM, DUAL, DEAD, TURNS>, Fwd<L>::T, cache, grid);
+}
+
 template <int L, bool IB, bool SYM, bool DUAL, int DEAD>
 static hipError_t launch_forward_LD(const float2* spec, int64_t N, const float2* bank, int K,
                                     int M, float* plane, int grid, const float2* bank2,
                                     hipStream_t s)
 {
-    static std::atomic<int> cache[64];
+    constexpr bool TURNS = Fwd<L>::kTurns;
+    constexpr bool CHOICE = (L == 2048 || L == 4096) &&
+                            (IB || SYM || (DUAL && (L == 2048 || DEAD > 0)));
     const int64_t nseg = (N + (L - M) - 1) / (L - M);
     if (grid <= 0) {
-        hipError_t e = resident_grid(forward_kernel<L, IB, SYM, DUAL, DEAD>, Fwd<L>::T, cache,
-                                     &grid);
+        hipError_t e = resident_forward<L, IB, SYM, DUAL, DEAD, TURNS>(&grid);
         if (e != hipSuccess)
             return e;
     }
     if ((int64_t)grid > nseg * K)
         grid = (int)(nseg * K);
-    hipLaunchKernelGGL((forward_kernel<L, IB, SYM, DUAL, DEAD>), dim3(grid), dim3(Fwd<L>::T), 0,
-                       s, spec, N, bank, K, M, nseg, plane, bank2);
+    if (CHOICE && nseg * K < (int64_t)kTurnItems * grid)
+        hipLaunchKernelGGL((forward_kernel<L, IB, SYM, DUAL, DEAD, !CHOICE && TURNS>), dim3(grid),
+                           dim3(Fwd<L>::T), 0, s, spec, N, bank, K, M, nseg, plane, bank2);
+    else
+        hipLaunchKernelGGL((forward_kernel<L, IB, SYM, DUAL, DEAD, TURNS>), dim3(grid),
+                           dim3(Fwd<L>::T), 0, s, spec, N, bank, K, M, nseg, plane, bank2);
     return hipGetLastError();
 }
 
@@ -1276,7 +1301,8 @@ template <int L, int E, int DEAD>
 static hipError_t resident_batched_LD(int* grid)
 {
     static std::atomic<int> cache[64];
-    const hipError_t e = resident_grid(batched_kernel<L, E, DEAD>, Fwd<L, E>::T, cache, grid);
+    const hipError_t e = resident_grid(batched_kernel<L, E, DEAD, Fwd<L, E>::kTurns>,
+                                       Fwd<L, E>::T, cache, grid);
     // Five of the eight workgroups that fit a CU: with all of them at work the 960 or 896
     // columns of each, in rows of any alignment, leave more half-written lines than
     // the caches hold until a neighbour completes them.  Spectra of odd length, K = 85,
@@ -1334,8 +1360,17 @@ static hipError_t launch_batched_LD(const float2* specs, const int64_t* offsets,
         if (e != hipSuccess)
             return e;
     }
-    hipLaunchKernelGGL((batched_kernel<L, E, DEAD>), dim3(grid), dim3(Fwd<L, E>::T), 0, s, specs,
-                       offsets, segpre, nspec, cap, bank, K, M, planes);
+    // the templates of a full batch; the smallest ones of the default kernels run without
+    // turns, the same 1 % as above (E = 8 is faster with them)
+    constexpr bool TURNS = Fwd<L, E>::kTurns;
+    constexpr bool CHOICE = (L == 2048 || L == 4096) && E == Geometry<L>::E;
+    if (CHOICE && cap / (L - M) * K < (int64_t)kTurnItems * grid)
+        hipLaunchKernelGGL((batched_kernel<L, E, DEAD, !CHOICE && TURNS>), dim3(grid),
+                           dim3(Fwd<L, E>::T), 0, s, specs, offsets, segpre, nspec, cap, bank, K,
+                           M, planes);
+    else
+        hipLaunchKernelGGL((batched_kernel<L, E, DEAD, TURNS>), dim3(grid), dim3(Fwd<L, E>::T), 0,
+                           s, specs, offsets, segpre, nspec, cap, bank, K, M, planes);
     return hipGetLastError();
 }
 

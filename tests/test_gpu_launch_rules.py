@@ -15,6 +15,39 @@ def _dev(a):
     return torch.from_numpy(np.ascontiguousarray(a)).cuda()
 
 
+# template count K, tap counts with no, one and two dead slots at each end
+@pytest.mark.parametrize("L,M", [(2048, 128), (2048, 256), (2048, 512), (4096, 256), (4096, 512),
+                                 (4096, 1024)])
+def test_templates_per_workgroup(L, M):
+    import torch
+    import paper_1804_05335_amd as fd
+    K, N = 9, 3 * (L - M) + 17
+    A, T = syn.random_spectrum(L + M, N), syn.random_taps(M, K, M)
+    T[:4] = np.conj(T[5:][::-1])                  # T_{-z} = conj T_z for the symmetric bank
+    T[4] = T[4].real
+    half = syn.random_taps(M + 1, K, M + 2)
+    a, bank = _dev(A), fd.prepare_bank(_dev(T), L)
+    sym, bh = fd.prepare_bank_sym(_dev(T), L), fd.prepare_bank(_dev(half), L)
+    items = 4 * K
+    ref = native.power(A, T)
+    # one template per workgroup, three, four (the first with turns), all in two
+    for grid in (items, 12, 9, 2):
+        got = {"plain": fd.correlate(a, bank, K, M, L, grid=grid),
+               "interbin": fd.correlate_interbin(a, bank, K, M, L, grid=grid),
+               "sym": fd.correlate_sym(a, sym, K, M, L, grid=grid),
+               "two-bin": fd.correlate_fourier2(a, bank, bh, K, M, L, grid=grid)}
+        if grid == items:
+            first = got
+            assert np.abs(got["plain"].cpu().numpy() - ref).max() <= TOL * ref.max()
+            assert np.abs(got["sym"].cpu().numpy() - ref).max() <= TOL * ref.max()
+            assert torch.equal(got["interbin"][:, ::2], got["plain"])
+            for c, want in ((0, ref), (1, native.power(A, half))):
+                plane = got["two-bin"][:, c::2].cpu().numpy()
+                assert np.abs(plane - want).max() <= TOL * want.max()
+        for name, plane in got.items():
+            assert torch.equal(plane, first[name]), (name, grid)
+
+
 @pytest.mark.parametrize("L,E", [(1024, 8), (2048, 8), (4096, 8), (2048, 16), (4096, 16)])
 def test_batch_smaller_than_the_grid(L, E):
     import torch

@@ -635,8 +635,8 @@ struct PassFFT {
 // both gradients three waves fit a SIMD instead of two, and a transform has two
 // barriers instead of three.  Measured for both gradients: 2^19 bins, K = 85, M =
 // 256, L = 2048 277 -> 219 us, L = 1024 258 -> 220 us, 300000 bins, K = 201, M =
-// 512, L = 4096 503 -> 468 us; the spectrum's alone 160 -> 159, 146 -> 146, 354
-// -> 358 us.  The forward kernels keep 16 values per lane from L = 1024 on: with
+// 512, L = 4096 503 -> 468 us; the spectrum's alone 160 -> 159, 146 -> 146 us (at
+// 4096 by size, see BwdGeometry::kSplitPoints).  The forward kernels keep 16 values per lane from L = 1024 on: with
 // four waves per SIMD of this transform the plane of 2^21 bins, K = 85, M = 256
 // took 252 us against 243, since its three exchanges move half as much again
 // through LDS.
@@ -865,6 +865,10 @@ struct SwapPlan { using R = typename Plan<L, E>::R; };
 template <> struct SwapPlan<8192, 16> { using R = SwapLast<16, 16, 16, 2>; };
 template <> struct SwapPlan<1024, 16> { using R = SwapLast<16, 16, 4>; };
 
+// L = 4096 with eight values per lane in passes over the whole workgroup, the same
+// arithmetic as the plan split over waves: see BwdGeometry::kSplitPoints.
+struct PassesPlan { using R = Radices<8, 8, 8, 8>; };
+
 // Values per lane of the forward kernels: 16 from L = 1024 on (two LDS exchanges
 // per transform, one at L = 1024; 2 waves per SIMD), fewer below so a
 // transform still spans at least one full wave.
@@ -901,6 +905,15 @@ struct BwdGeometry {
     // bins, K = 85) 1 / 2 / 3 / 4 windows took 0.349 / 0.387 / 0.300 /
     // 0.669 ms (two waves per SIMD from two windows on, spills at four)
     static constexpr int kWinGroupEdge = L <= 512 ? FDAS_BWD_GROUP : 1;
+    // At L = 4096 the spectrum's gradient alone, and both with M/2 = T, take the plan
+    // split over waves below this many points of the plane (K N) and passes from it
+    // on: where the weights no longer come from the last-level cache, its one
+    // workgroup per CU hides less of their latency.  Measured (us), passes -> split:
+    // spectrum's gradient, M = 512: K = 85, N = 300000 231 -> 230, K = 201, N = 100003
+    // 222 -> 221, K = 161, N = 300000 308 -> 312, K = 301, N = 600000 794 -> 817; both
+    // gradients, M = 1024: K = 85, N = 200000 229 -> 229, K = 201, N = 300000 546 -> 557,
+    // K = 301, N = 600000 1326 -> 1361.  The other kernels gain at every size.
+    static constexpr int64_t kSplitPoints = int64_t(1) << 25, kSplitPointsEdge = int64_t(1) << 24;
 };
 
 }  // namespace fdas

@@ -279,11 +279,11 @@ constexpr float kQuarterPi2 = 0.61685027506808491368f;   // (pi/4)^2, interbinni
 // Nothing but the valid plane values reaches HBM (Sec. 4.2 first paragraph).
 // The LDS ping-pong buffers la/lb keep alternating across calls, so a
 // workgroup's consecutive work needs no extra barrier.
-template <int L, int EV = Geometry<L>::E, bool IB_PLAN = false>
+template <int L, int EV = Geometry<L>::E, class PLAN = SwapPlan<L, EV>>
 struct Fwd {
     static constexpr bool kTurns = L >= 1024 && L <= 4096;    // see give_way
     static constexpr int E = EV;
-    using F = FFT<L, E, typename std::conditional_t<IB_PLAN && L == 8192, Plan<L, E>, SwapPlan<L, E>>::R>;
+    using F = FFT<L, E, typename PLAN::R>;
     static constexpr int T = F::T;
     static constexpr int NTW = F::NTW;
     // interbinned epilogue: waves per workgroup, and the `edge` slots
@@ -548,7 +548,9 @@ __global__ __launch_bounds__(Fwd<L>::T, 2) void forward_kernel(
     const float2* __restrict__ spec, int64_t N, const float2* __restrict__ bank, int K, int M,
     int64_t nseg, float* __restrict__ plane, const float2* __restrict__ bank2)
 {
-    using W = Fwd<L, Geometry<L>::E, IB>;
+    // the interbinned kernel's neighbouring outputs must sit in neighbouring lanes
+    constexpr int E = Geometry<L>::E;
+    using W = Fwd<L, E, std::conditional_t<IB && L == 8192, Plan<L, E>, SwapPlan<L, E>>>;
     __shared__ __align__(16) float2 lds[W::F::kLds];
     __shared__ float2 twl[W::F::kLdsTwAlloc];
     __shared__ __align__(16) float2 edge[IB ? W::kEdgeAlloc : 1];   // interbinning
@@ -701,9 +703,9 @@ __global__ __launch_bounds__((Fwd<L, E>::T), 2) void batched_kernel(
 // windows' contributions gives the exact gradients.  Y is recomputed, never
 // stored.  Window contributions go to per-(chunk, window) partial buffers and
 // are summed in FP64, in a fixed order, by the two reduction kernels.
-template <int L>
+template <int L, class PLAN = SwapPlan<L, BwdGeometry<L>::E>>
 struct Bwd {
-    using W = Fwd<L, BwdGeometry<L>::E>;
+    using W = Fwd<L, BwdGeometry<L>::E, PLAN>;
     using F = typename W::F;
     static constexpr int E = W::E;
     static constexpr int T = W::T;
@@ -921,14 +923,14 @@ struct Bwd {
     }
 };
 
-template <int L, bool WANT_T, bool EDGE>
+template <int L, bool WANT_T, bool EDGE, class PLAN = SwapPlan<L, BwdGeometry<L>::E>>
 __global__ __launch_bounds__(Bwd<L>::T, WANT_T ? BwdGeometry<L>::kMinWaves
                                                : BwdGeometry<L>::kMinWavesSpec) void backward_kernel(
     const float2* __restrict__ spec, int64_t N, const float2* __restrict__ bank, int K, int M,
     int zchunk, int64_t nwin, const float* __restrict__ dLdP, int want_A,
     float2* __restrict__ partA, float2* __restrict__ partT)
 {
-    using Bk = Bwd<L>;
+    using Bk = Bwd<L, PLAN>;
     __shared__ __align__(16) float2 lds[Bk::F::kLds];
     __shared__ float2 twl[Bk::F::kLdsTwAlloc];
     const int t = Bk::F::place(threadIdx.x);
@@ -1061,7 +1063,7 @@ __global__ void reduce_grad_taps_final_kernel(const double2* __restrict__ tpart,
 // blockIdx.x), as in the single-spectrum kernel, so the body allocates the
 // same registers (a grid-stride loop over windows made the compiler keep
 // more values live and spill).
-template <int L, bool WANT_T, bool EDGE>
+template <int L, bool WANT_T, bool EDGE, class PLAN = SwapPlan<L, BwdGeometry<L>::E>>
 __global__ __launch_bounds__(Bwd<L>::T, WANT_T ? BwdGeometry<L>::kMinWaves
                                                : BwdGeometry<L>::kMinWavesSpec) void
 backward_batched_kernel(const float2* __restrict__ specs, const int64_t* __restrict__ offsets,
@@ -1070,7 +1072,7 @@ backward_batched_kernel(const float2* __restrict__ specs, const int64_t* __restr
                         const float* __restrict__ dLdP, int want_A, float2* __restrict__ partA,
                         float2* __restrict__ partT)
 {
-    using Bk = Bwd<L>;
+    using Bk = Bwd<L, PLAN>;
     __shared__ __align__(16) float2 lds[Bk::F::kLds];
     __shared__ float2 twl[Bk::F::kLdsTwAlloc];
     const int64_t nw = min(winpre[nspec], maxwin);
@@ -1474,6 +1476,15 @@ hipError_t launch_batched(const float2* specs, const int64_t* offsets, int nspec
     }
 }
 
+// Whether the adjoint at L = 4096 runs in passes over the workgroup
+// (BwdGeometry::kSplitPoints); points: of the plane, or of all planes of a batch.
+template <int L>
+static bool by_passes(int64_t points, int want_T, bool edge)
+{
+    return want_T ? edge && points >= BwdGeometry<L>::kSplitPointsEdge
+                  : points >= BwdGeometry<L>::kSplitPoints;
+}
+
 template <int L>
 static hipError_t launch_backward_L(const float2* spec, int64_t N, const float2* bank, int K,
                                    int M, int zchunk, int64_t nwin, const float* dLdP,
@@ -1488,15 +1499,25 @@ static hipError_t launch_backward_L(const float2* spec, int64_t N, const float2*
     // instructions and cycles); without it the compiler waits for the w
     // loads early in the transform and the kernel ran slower, so the
     // spectrum-only kernel keeps the general form.
-    if (want_T && M / 2 == Bwd<L>::T)
-        hipLaunchKernelGGL((backward_kernel<L, true, true>), grid_t, dim3(Bwd<L>::T), 0, s, spec,
-                           N, bank, K, M, zchunk, nwin, dLdP, want_A, partA, partT);
-    else if (want_T)
-        hipLaunchKernelGGL((backward_kernel<L, true, false>), grid_t, dim3(Bwd<L>::T), 0, s, spec,
-                           N, bank, K, M, zchunk, nwin, dLdP, want_A, partA, partT);
-    else
-        hipLaunchKernelGGL((backward_kernel<L, false, false>), grid, dim3(Bwd<L>::T), 0, s, spec,
-                           N, bank, K, M, zchunk, nwin, dLdP, want_A, partA, partT);
+    const bool edge = M / 2 == Bwd<L>::T;
+    auto launch = [&](auto kernel, dim3 g) {
+        hipLaunchKernelGGL(kernel, g, dim3(Bwd<L>::T), 0, s, spec, N, bank, K, M, zchunk, nwin,
+                           dLdP, want_A, partA, partT);
+    };
+    if (L == 4096 && by_passes<L>((int64_t)K * N, want_T, edge)) {
+        if constexpr (L == 4096) {
+            if (want_T)
+                launch(backward_kernel<L, true, true, PassesPlan>, grid_t);
+            else
+                launch(backward_kernel<L, false, false, PassesPlan>, grid);
+        }
+    } else if (want_T && edge) {
+        launch(backward_kernel<L, true, true>, grid_t);
+    } else if (want_T) {
+        launch(backward_kernel<L, true, false>, grid_t);
+    } else {
+        launch(backward_kernel<L, false, false>, grid);
+    }
     return hipGetLastError();
 }
 
@@ -1588,18 +1609,25 @@ static hipError_t launch_backward_batched_L(const float2* specs, const int64_t* 
     const dim3 grid = grid_for(maxwin);
     const int NW = backward_window_group(L, M);
     const dim3 grid_t = grid_for((maxwin + NW - 1) / NW);
-    if (want_T && M / 2 == Bwd<L>::T)
-        hipLaunchKernelGGL((backward_batched_kernel<L, true, true>), grid_t, dim3(Bwd<L>::T), 0,
-                           s, specs, offsets, winpre, nspec, cap, bank, K, M, zchunk, maxwin, dLdP,
-                           want_A, partA, partT);
-    else if (want_T)
-        hipLaunchKernelGGL((backward_batched_kernel<L, true, false>), grid_t, dim3(Bwd<L>::T), 0,
-                           s, specs, offsets, winpre, nspec, cap, bank, K, M, zchunk, maxwin, dLdP,
-                           want_A, partA, partT);
-    else
-        hipLaunchKernelGGL((backward_batched_kernel<L, false, false>), grid, dim3(Bwd<L>::T), 0,
-                           s, specs, offsets, winpre, nspec, cap, bank, K, M, zchunk, maxwin, dLdP,
-                           want_A, partA, partT);
+    const bool edge = M / 2 == Bwd<L>::T;
+    auto launch = [&](auto kernel, dim3 g) {
+        hipLaunchKernelGGL(kernel, g, dim3(Bwd<L>::T), 0, s, specs, offsets, winpre, nspec, cap,
+                           bank, K, M, zchunk, maxwin, dLdP, want_A, partA, partT);
+    };
+    if (L == 4096 && by_passes<L>((int64_t)K * cap, want_T, edge)) {
+        if constexpr (L == 4096) {
+            if (want_T)
+                launch(backward_batched_kernel<L, true, true, PassesPlan>, grid_t);
+            else
+                launch(backward_batched_kernel<L, false, false, PassesPlan>, grid);
+        }
+    } else if (want_T && edge) {
+        launch(backward_batched_kernel<L, true, true>, grid_t);
+    } else if (want_T) {
+        launch(backward_batched_kernel<L, true, false>, grid_t);
+    } else {
+        launch(backward_batched_kernel<L, false, false>, grid);
+    }
     return hipGetLastError();
 }
 

@@ -69,3 +69,33 @@ def test_batch_smaller_than_the_grid(L, E):
             plane = first[K * at:K * (at + len(a))].view(K, -1).cpu().numpy()
             assert np.abs(plane - ref).max() <= TOL * ref.max()
         at += len(a)
+
+
+@pytest.mark.parametrize("M,taps", [(512, False), (1024, False), (1024, True)])
+def test_adjoint_plans_at_4096(M, taps):
+    # the batch's planes have 2^25 points or more, each spectrum's fewer than 2^24
+    import torch
+    import paper_1804_05335_amd as fd
+    L, K, lens = 4096, 801, [20000, 15001, 7000]
+    assert K * sum(lens) >= 1 << 25 and K * max(lens) < 1 << 24
+    g = torch.Generator(device="cuda").manual_seed(M)
+    s = torch.randn(sum(lens), dtype=torch.complex64, device="cuda", generator=g)
+    T = torch.randn(K, M, dtype=torch.complex64, device="cuda", generator=g) / M ** 0.5
+    w = torch.rand(K * sum(lens), device="cuda", generator=g)
+    bank = fd.prepare_bank(T, L)
+    offs = torch.tensor([0] + list(np.cumsum(lens)), device="cuda")
+    gs, gt = fd.correlate_backward_batched(s, offs, bank, K, M, L, w, want_taps=taps, zchunk=100)
+    at, total = 0, 0
+    for n in lens:
+        one, t = torch.empty(n, dtype=torch.complex64, device="cuda"), None
+        if taps:
+            t = torch.empty(K, M, dtype=torch.complex64, device="cuda")
+        ws = torch.empty(fd.fdas_backward_workspace_bytes(n, K, M, L, 100), dtype=torch.uint8,
+                         device="cuda")
+        fd.fdas_correlate_backward_ex(s[at:at + n], n, bank, K, M, L,
+                                      w[K * at:K * (at + n)].view(K, n), one, t, 100, ws)
+        assert torch.equal(one, gs[at:at + n])
+        total = total + t if taps else 0
+        at += n
+    if taps:
+        assert (gt - total).abs().max() <= TOL * total.abs().max()

@@ -237,18 +237,41 @@ hipError_t launch_prepare_bank(const float2* taps, int K, int M, int L, float2* 
 // below L = 1024, whose one-wave workgroups pay more for the branch than they
 // gain (300001 bins, K = 85, M = 64, L = 512: 39.1 -> 41.5 us), nor at L = 8192,
 // where one workgroup fills the CU and the two-bin kernel has no register to
-// spare for the count (709 -> 1020 us).  At L = 2048 and 4096 the half-bin, symmetric
-// and two-bin kernels also run without (TURNS false) where a workgroup has fewer than
-// kTurnItems templates: there is nothing to catch up with, and the branches cost the
-// half-bin plane of 13476 bins (K = 121, M = 512, L = 2048) 13.6 -> 13.8 us, the
-// two-bin plane at L = 4096 16.9 -> 17.2 (two spilled registers).  The plain kernel and
-// the two-bin kernel with no dead slots at L = 4096, which turns leave with fewer spills,
-// are the faster with turns there too (13.8 -> 13.4 and 20.5 -> 18.1 us).
+// spare for the count (709 -> 1020 us).
+//
+// Where a workgroup has one or two templates there is little to catch up with, and
+// the branches, or the registers they take, cost 1 to 4 %.  At L = 2048 and 4096 the
+// kernels that lose are built without turns too, for the calls below so many eighths
+// of a template per workgroup (turn_eighths).  Time without turns / with them, on
+// planes of K = 85 (the largest and smallest of three tap counts):
+//   templates per workgroup        1          1.5         2          3          4
+//   half-bin,  L = 2048       0.99 0.99   0.98 0.99   1.00 1.02  1.00 1.04  1.02 1.05
+//              L = 4096       0.99 1.00   0.99 0.99   1.02 1.08  1.07 1.10  1.07 1.08
+//   symmetric, L = 2048       0.98 0.99   0.96 0.98   0.99 1.00  0.99 1.00  0.99 1.00
+//              L = 4096       0.99 1.01   0.99 1.00   1.00 1.02  1.02 1.03  1.02 1.03
+//   two-bin,   L = 2048       0.99 1.00   1.00 1.00   1.00 1.01  1.01 1.03  1.01 1.03
+//              L = 4096       0.98 0.99   1.00 1.01   0.99 0.99  1.03 1.03  1.02 1.07
+//   batched,   L = 2048       0.99 1.00   0.98 1.00   0.99 1.01  1.00 1.00  1.00 1.01
+//              L = 4096       0.99 0.99   0.99 1.00   1.00 1.01  1.00 1.01  1.02 1.02
+// The plain kernel (13.8 -> 13.4 us at L = 4096) and the two-bin kernel with no dead
+// slots at L = 4096 (20.5 -> 18.1: fewer spilled registers) gain at every size.
 // Kernels of other streams on the same CU run at priority 0 and yield to the waves
 // above it.  Measured beside the plane of 2^21 bins without turns -> with: a copy of 64 MB
 // 33.7 -> 34.7 us a call, a candidate search of 85 x 2^18 71.5 -> 58.3, an addition of 4096
 // values 4.4 -> 4.7; beside the half-bin plane 40.2 -> 41.9, 63.5 -> 57.3, 4.5 -> 4.6.
-constexpr int kTurnItems = 4;
+template <int L, bool IB, bool SYM, bool DUAL, int DEAD, bool BATCH>
+constexpr int turn_eighths()
+{
+    if (L != 2048 && L != 4096)
+        return 0;
+    if (BATCH)
+        return L == 2048 ? 24 : 14;
+    if (SYM)
+        return L == 2048 ? 32 : 0;
+    if (DUAL)
+        return L == 2048 ? 16 : (DEAD > 0 ? 12 : 0);
+    return IB ? 13 : 0;
+}
 
 __device__ __forceinline__ void give_way(int n)
 {
@@ -1221,8 +1244,7 @@ static hipError_t launch_forward_LD(const float2* spec, int64_t N, const float2*
                                     hipStream_t s)
 {
     constexpr bool TURNS = Fwd<L>::kTurns;
-    constexpr bool CHOICE = (L == 2048 || L == 4096) &&
-                            (IB || SYM || (DUAL && (L == 2048 || DEAD > 0)));
+    constexpr int FEW = turn_eighths<L, IB, SYM, DUAL, DEAD, false>();
     const int64_t nseg = (N + (L - M) - 1) / (L - M);
     if (grid <= 0) {
         hipError_t e = resident_forward<L, IB, SYM, DUAL, DEAD, TURNS>(&grid);
@@ -1231,8 +1253,8 @@ static hipError_t launch_forward_LD(const float2* spec, int64_t N, const float2*
     }
     if ((int64_t)grid > nseg * K)
         grid = (int)(nseg * K);
-    if (CHOICE && nseg * K < (int64_t)kTurnItems * grid)
-        hipLaunchKernelGGL((forward_kernel<L, IB, SYM, DUAL, DEAD, !CHOICE && TURNS>), dim3(grid),
+    if (8 * nseg * K < (int64_t)FEW * grid)
+        hipLaunchKernelGGL((forward_kernel<L, IB, SYM, DUAL, DEAD, FEW == 0 && TURNS>), dim3(grid),
                            dim3(Fwd<L>::T), 0, s, spec, N, bank, K, M, nseg, plane, bank2);
     else
         hipLaunchKernelGGL((forward_kernel<L, IB, SYM, DUAL, DEAD, TURNS>), dim3(grid),
@@ -1362,12 +1384,11 @@ static hipError_t launch_batched_LD(const float2* specs, const int64_t* offsets,
         if (e != hipSuccess)
             return e;
     }
-    // the templates of a full batch; the smallest ones of the default kernels run without
-    // turns, the same 1 % as above (E = 8 is faster with them)
+    // the templates of a full batch (E = 8 is faster with turns at every size)
     constexpr bool TURNS = Fwd<L, E>::kTurns;
-    constexpr bool CHOICE = (L == 2048 || L == 4096) && E == Geometry<L>::E;
-    if (CHOICE && cap / (L - M) * K < (int64_t)kTurnItems * grid)
-        hipLaunchKernelGGL((batched_kernel<L, E, DEAD, !CHOICE && TURNS>), dim3(grid),
+    constexpr int FEW = E == Geometry<L>::E ? turn_eighths<L, false, false, false, DEAD, true>() : 0;
+    if (8 * (cap / (L - M)) * K < (int64_t)FEW * grid)
+        hipLaunchKernelGGL((batched_kernel<L, E, DEAD, FEW == 0 && TURNS>), dim3(grid),
                            dim3(Fwd<L, E>::T), 0, s, specs, offsets, segpre, nspec, cap, bank, K,
                            M, planes);
     else

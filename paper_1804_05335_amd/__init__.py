@@ -215,7 +215,9 @@ def harmonic_sums(plane, max_fold: int):
 
 
 # fdas_candidate as numpy reads it, and the records of each list that travel
-# with the counts (longer lists are fetched in a second transfer)
+# with the counts; longer lists are fetched in a second transfer, 15 us each.
+# Reading six lists of 40 records takes 35 us with 64 of each, 47 with 512, 49 with
+# 1024, 63 with 4096; one list 23 us up to 512 and 31 from 1024 on.
 _RECORD = [("r", "<i8"), ("row", "<i4"), ("power", "<f4")]
 _FIRST_RECORDS = 512
 
@@ -256,7 +258,9 @@ class _CandidateLists:
 def _by_row(found):
     import numpy as np
     rec, n = found
-    rec = rec[np.lexsort((rec["r"], rec["row"]))]
+    # row and bin (at most 2^32) in one key: 65536 records take 0.5 ms in any order, by
+    # lexsort 2.7 to 3.3, the more the further the list is from this order
+    rec = rec[np.argsort(rec["row"].astype(np.int64) << 40 | rec["r"])]
     return rec["r"].copy(), rec["row"].copy(), rec["power"].copy(), n
 
 
@@ -340,7 +344,7 @@ def _by_spectrum(found, offs):
     rec, n = found
     spec = np.searchsorted(offs, rec["r"], side="right") - 1
     r = rec["r"] - offs[spec]
-    order = np.lexsort((r, rec["row"], spec))
+    order = np.lexsort((r, spec << 12 | rec["row"]))       # K is at most 4096
     return spec[order], r[order], rec["row"][order].copy(), rec["power"][order].copy(), n
 
 

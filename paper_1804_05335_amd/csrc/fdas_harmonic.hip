@@ -75,8 +75,12 @@ __device__ __forceinline__ int fold_chunk(int p, int P)
 // Work item l of [0, P rows): a chunk (place p in the octave order) and a row.
 // Consecutive workgroups go to the 8 XCDs in turn, each with an L2 of its own, so
 // the items are dealt out in runs of kFoldRun places x all rows per XCD: the
-// waves that share lines share an L2.
-constexpr int kFoldRun = 32, kXcds = 8;
+// waves that share lines share an L2.  (The host emulation of the tests builds with a
+// short run, to reach several rounds.)
+#ifndef FDAS_FOLD_RUN
+#define FDAS_FOLD_RUN 32
+#endif
+constexpr int kFoldRun = FDAS_FOLD_RUN, kXcds = 8;
 
 __device__ __forceinline__ void fold_item(int64_t l, int P, int rows, int& p, int& row)
 {

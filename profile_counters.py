@@ -202,7 +202,8 @@ def main() -> int:
     lines += ["",
               f"GRBM_GUI_ACTIVE / {XCDS} XCDs = {cycles:.4g} cycles per dispatch.",
               f"VALU issue: SQ_INSTS_VALU x 4 cycles / (cycles x {SIMDS} SIMDs) = "
-              f"{100 * issue:.1f} % of the VALU issue slots."]
+              f"{100 * issue:.1f} % of one instruction in four cycles (several waves of a SIMD "
+              "retire up to one in two: profiles/issue_and_lds_rates.md)."]
     if "SQ_INSTS_LDS" in mean and "SQ_LDS_BANK_CONFLICT" in mean:
         lines.append(f"LDS: SQ_LDS_BANK_CONFLICT = {mean['SQ_LDS_BANK_CONFLICT']:.4g} cycles for "
                      f"SQ_INSTS_LDS = {mean['SQ_INSTS_LDS']:.4g} instructions "

@@ -293,7 +293,13 @@ __global__ __launch_bounds__(kHarmThreads) void harmonic_sum_kernel(
 //   rows, 201 x 29908 4.0 -> 4.2 but 1025 x 30000 14.5 -> 12.6;
 //   H = 4, 8 from the plane: 85 x 2^20 39 -> 32, 34 -> 30; 85 x 2^22 153 -> 161, 124 ->
 //   130; 16: 29 -> 26, 103 -> 99;
-//   H = 32 and 64: 85 x 2^22 91 -> 88, 49 -> 17, 1025 x 30000 24 -> 9, 25 -> 12.5.
+//   H = 32 and 64 of small folds, H = 64 of large ones and 32 from the plane: 1025 x 30000
+//   24 -> 9, 25 -> 12.5, 85 x 2^22 49 -> 17 (64), 122 -> 116 (32 from the plane);
+//   H = 32 on top of the fold below, from 2^17 points of the fold on: at most one workgroup
+//   of this kernel per CU, 41 x 6291456 37 -> 44, 401 x 496989 45 -> 49, 85 x 2097153 40.5 ->
+//   42.8 (85 x 2^21 39.8 -> 38.4); the second only on some, 85 x 3000001 74 -> 62, 401 x
+//   640000 71 -> 63, but one row of 265625 columns 55 -> 60; two on most, 85 x 5000000 103 ->
+//   107, 401 x 2^20 96 -> 100; more, 85 x 5600000 129 -> 116, 85 x 2^23 175 -> 172.
 bool one_fold_by_chain(int64_t N, int K, int H, int64_t NH, int KH, bool prev)
 {
     const int64_t points = N * K, blocks = (NH + kHarmCols - 1) / kHarmCols * KH;
@@ -301,6 +307,8 @@ bool one_fold_by_chain(int64_t N, int K, int H, int64_t NH, int KH, bool prev)
         return points >= 1 << 23;
     if (H == 2)
         return points < 1 << 21 || (points >= 1 << 23 && KH > 1);
+    if (H == 32 && prev && NH * KH >= 1 << 17)
+        return blocks > 512 || (blocks > 256 && blocks <= 384 && KH > 1);
     if (H >= 32)
         return true;
     if (!prev)

@@ -16,6 +16,9 @@ pytestmark = pytest.mark.gpu
     (41, 131073, (4, 8, 16)),                   # 363 workgroups, then too few
     (85, 200003, (4, 8, 16, 32)),               # 16 from 256 workgroups on
     (257, 65529, (4,)), (257, 65537, (4,)),     # rows below and from 2^14 columns on
+    (1, (1 << 22) - 32, (32,)), (1, 1 << 22, (32,)),                          # 2^17 points
+    (1, 1 << 24, (32,)), (1, (1 << 24) + 1, (32,)),                           # 512 workgroups
+    (65, 1400001, (32,)),                       # 129 workgroups in three rows
 ])
 def test_one_fold(K, N, folds):
     import torch
